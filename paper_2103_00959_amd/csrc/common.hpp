@@ -52,6 +52,13 @@ __device__ __forceinline__ uint32_t f32_to_f16(float f)
     return b;
 }
 
+// Vectors at element alignment only: gfx950 serves vector memory accesses at any
+// byte address with the same instructions, so rows of odd widths are read and
+// written in 16-byte words too.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_u __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(2)));
+
 // Load VEC consecutive elements (VEC * bytes is 4, 8 or 16, or VEC == 1)
 // starting at element index `idx` and widen them to fp32.
 template <typename T, int VEC>
@@ -60,7 +67,7 @@ __device__ __forceinline__ void load_vec(const T *__restrict__ base, int64_t idx
 template <>
 __device__ __forceinline__ void load_vec<float, 4>(const float *__restrict__ p, int64_t i, float (&o)[4])
 {
-    float4 v = *reinterpret_cast<const float4 *>(p + i);
+    const f32x4_u v = *reinterpret_cast<const f32x4_u *>(p + i);
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
 }
 template <>
@@ -71,7 +78,7 @@ __device__ __forceinline__ void load_vec<float, 1>(const float *__restrict__ p, 
 template <>
 __device__ __forceinline__ void load_vec<bf16_t, 8>(const bf16_t *__restrict__ p, int64_t i, float (&o)[8])
 {
-    uint4 v = *reinterpret_cast<const uint4 *>(p + i);
+    const u32x4_u v = *reinterpret_cast<const u32x4_u *>(p + i);
     o[0] = bf16_lo(v.x); o[1] = bf16_hi(v.x); o[2] = bf16_lo(v.y); o[3] = bf16_hi(v.y);
     o[4] = bf16_lo(v.z); o[5] = bf16_hi(v.z); o[6] = bf16_lo(v.w); o[7] = bf16_hi(v.w);
 }
@@ -83,7 +90,7 @@ __device__ __forceinline__ void load_vec<bf16_t, 1>(const bf16_t *__restrict__ p
 template <>
 __device__ __forceinline__ void load_vec<f16_t, 8>(const f16_t *__restrict__ p, int64_t i, float (&o)[8])
 {
-    uint4 v = *reinterpret_cast<const uint4 *>(p + i);
+    const u32x4_u v = *reinterpret_cast<const u32x4_u *>(p + i);
     uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -104,13 +111,13 @@ __device__ __forceinline__ void store_vec(T *__restrict__ base, int64_t idx, con
 template <>
 __device__ __forceinline__ void store_vec<float, 4>(float *__restrict__ p, int64_t i, const float (&v)[4])
 {
-    *reinterpret_cast<float4 *>(p + i) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<f32x4_u *>(p + i) = f32x4_u{v[0], v[1], v[2], v[3]};
 }
 template <>
 __device__ __forceinline__ void store_vec<float, 8>(float *__restrict__ p, int64_t i, const float (&v)[8])
 {
-    *reinterpret_cast<float4 *>(p + i) = make_float4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<float4 *>(p + i + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    *reinterpret_cast<f32x4_u *>(p + i) = f32x4_u{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<f32x4_u *>(p + i + 4) = f32x4_u{v[4], v[5], v[6], v[7]};
 }
 template <>
 __device__ __forceinline__ void store_vec<float, 1>(float *__restrict__ p, int64_t i, const float (&v)[1])
@@ -120,20 +127,20 @@ __device__ __forceinline__ void store_vec<float, 1>(float *__restrict__ p, int64
 template <>
 __device__ __forceinline__ void store_vec<bf16_t, 8>(bf16_t *__restrict__ p, int64_t i, const float (&v)[8])
 {
-    uint4 w;
+    u32x4_u w;
     w.x = f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16);
     w.y = f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16);
     w.z = f32_to_bf16(v[4]) | (f32_to_bf16(v[5]) << 16);
     w.w = f32_to_bf16(v[6]) | (f32_to_bf16(v[7]) << 16);
-    *reinterpret_cast<uint4 *>(p + i) = w;
+    *reinterpret_cast<u32x4_u *>(p + i) = w;
 }
 template <>
 __device__ __forceinline__ void store_vec<bf16_t, 4>(bf16_t *__restrict__ p, int64_t i, const float (&v)[4])
 {
-    uint2 w;
+    u32x2_u w;
     w.x = f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16);
     w.y = f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16);
-    *reinterpret_cast<uint2 *>(p + i) = w;
+    *reinterpret_cast<u32x2_u *>(p + i) = w;
 }
 template <>
 __device__ __forceinline__ void store_vec<bf16_t, 1>(bf16_t *__restrict__ p, int64_t i, const float (&v)[1])
@@ -143,20 +150,20 @@ __device__ __forceinline__ void store_vec<bf16_t, 1>(bf16_t *__restrict__ p, int
 template <>
 __device__ __forceinline__ void store_vec<f16_t, 8>(f16_t *__restrict__ p, int64_t i, const float (&v)[8])
 {
-    uint4 w;
+    u32x4_u w;
     w.x = f32_to_f16(v[0]) | (f32_to_f16(v[1]) << 16);
     w.y = f32_to_f16(v[2]) | (f32_to_f16(v[3]) << 16);
     w.z = f32_to_f16(v[4]) | (f32_to_f16(v[5]) << 16);
     w.w = f32_to_f16(v[6]) | (f32_to_f16(v[7]) << 16);
-    *reinterpret_cast<uint4 *>(p + i) = w;
+    *reinterpret_cast<u32x4_u *>(p + i) = w;
 }
 template <>
 __device__ __forceinline__ void store_vec<f16_t, 4>(f16_t *__restrict__ p, int64_t i, const float (&v)[4])
 {
-    uint2 w;
+    u32x2_u w;
     w.x = f32_to_f16(v[0]) | (f32_to_f16(v[1]) << 16);
     w.y = f32_to_f16(v[2]) | (f32_to_f16(v[3]) << 16);
-    *reinterpret_cast<uint2 *>(p + i) = w;
+    *reinterpret_cast<u32x2_u *>(p + i) = w;
 }
 template <>
 __device__ __forceinline__ void store_vec<f16_t, 1>(f16_t *__restrict__ p, int64_t i, const float (&v)[1])
@@ -236,8 +243,8 @@ struct RowGather {
             const auto w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
             return make_uint4(w[0], w[1], w[2], w[3]);
         } else {
-            const uint4 v = *reinterpret_cast<const uint4 *>(base + (ok ? idx : 0));
-            return ok ? v : make_uint4(0u, 0u, 0u, 0u);
+            const u32x4_u v = *reinterpret_cast<const u32x4_u *>(base + (ok ? idx : 0));
+            return ok ? make_uint4(v.x, v.y, v.z, v.w) : make_uint4(0u, 0u, 0u, 0u);
         }
     }
 

@@ -218,6 +218,10 @@ struct RowMap {
     int n_slabs = 1;
 };
 
+// The same with 16-byte vectors at any alignment and any width of at least one
+// vector (the kernel moves a row's last vector back to the row's end).  Rows of
+// 41 bf16 classes take 6 lanes of 8 instead of 41 element lanes of 64.
+RowMap span_map(int64_t width, int elem_bytes);
 RowMap row_map(int64_t width, int elem_bytes, int unit_elems /* vec must divide it */,
                bool aligned16);
 

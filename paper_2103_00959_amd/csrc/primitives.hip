@@ -483,11 +483,12 @@ hipError_t radix_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, ui
     return hipSuccess;
 }
 
-RowMap row_map(int64_t width, int elem_bytes, int unit_elems, bool aligned16)
+namespace {
+
+RowMap lane_map(int64_t width, int vec)
 {
     RowMap m;
-    const int v16 = 16 / elem_bytes;
-    m.vec = (aligned16 && width % v16 == 0 && unit_elems % v16 == 0) ? v16 : 1;
+    m.vec = vec;
     const int64_t lanes = (width + m.vec - 1) / m.vec;
     if (lanes <= kWave) {
         m.S = next_pow2((int)(lanes > 0 ? lanes : 1));
@@ -502,6 +503,20 @@ RowMap row_map(int64_t width, int elem_bytes, int unit_elems, bool aligned16)
     m.n_slabs = (int)((width + m.slab - 1) / m.slab);
     if (m.n_slabs < 1) m.n_slabs = 1;
     return m;
+}
+
+}  // namespace
+
+RowMap row_map(int64_t width, int elem_bytes, int unit_elems, bool aligned16)
+{
+    const int v16 = 16 / elem_bytes;
+    return lane_map(width, (aligned16 && width % v16 == 0 && unit_elems % v16 == 0) ? v16 : 1);
+}
+
+RowMap span_map(int64_t width, int elem_bytes)
+{
+    const int v16 = 16 / elem_bytes;
+    return lane_map(width, width >= v16 ? v16 : 1);
 }
 
 }  // namespace cogdl

@@ -51,8 +51,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm_reduce(const int4 *__restrict__
         const int np = d.z;
         const float scale = (mean && d.w > 0) ? 1.f / (float)d.w : 1.f;
         for (int64_t fb = 0; fb < F; fb += kWave * VEC) {
-            const int64_t f = fb + (int64_t)lane * VEC;
+            int64_t f = fb + (int64_t)lane * VEC;
             if (f >= F) continue;
+            if (f + VEC > F) f = F - VEC;      // the row's last VEC features (overlap: same bits)
             float c[4][VEC];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -173,13 +174,11 @@ cogdl_status max_reduce_launch(const char *name, const Plan &P, int64_t F, void 
 
 }  // namespace
 
-// Four features per lane when the rows allow 16-byte partial loads and
-// aligned output stores, one otherwise.
+// Four features per lane, one for rows narrower than that.
 cogdl_status sum_reduce_launch(const char *name, const Plan &P, int64_t F, void *Y, int ydt,
                                bool mean, const float *bias, int act, hipStream_t s)
 {
-    const int ybytes = dtype_bytes(ydt);
-    if (F % 4 == 0 && (uintptr_t)Y % (4 * ybytes) == 0)
+    if (F >= 4)
         return reduce_launch_v<4>(name, P, F, Y, ydt, mean, bias, act, s);
     return reduce_launch_v<1>(name, P, F, Y, ydt, mean, bias, act, s);
 }
@@ -214,9 +213,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     if (P && (P->n_rows != out_rows || P->nnz != nnz || P->max_feat < F)) return COGDL_ERR_PLAN;
     if (out_rows == 0 || F == 0) return COGDL_OK;
 
-    const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)Y % 16 == 0) &&
-                         (!maxr || !arg || (uintptr_t)arg % 16 == 0);
-    const RowMap m = row_map(F, dtype_bytes(xdt), F, aligned);
+    const RowMap m = span_map(F, dtype_bytes(xdt));
     SpmmArgs a;
     a.units = P ? P->units : nullptr;
     a.u_lo = nullptr;

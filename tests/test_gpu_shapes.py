@@ -1,0 +1,105 @@
+"""GPU parity at the shapes where the kernels' vector maps change: widths around whole 16-byte
+vectors, buffers at element alignment, guard elements around every output."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2103_00959_amd import synth
+
+from gpu_util import features, graph_to_dev, say, scaled_error, to_f64, tol_for
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 24
+
+
+@pytest.fixture(scope="module")
+def cg():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2103_00959_amd as m
+    m.lib()
+    return m
+
+
+def _graph(seed=0, n=700, m=450):
+    """Empty rows, rows of one to a few edges, and rows of several hundred (split at group size 40)."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(0, 14, n)
+    deg[rng.choice(n, 8, replace=False)] = rng.integers(41, 420, 8)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.sort(rng.choice(m, d, replace=False)) for d in deg]).astype(np.int32)
+    col[:3] = m - 1                      # the last row of X, whose last vector ends the buffer
+    val = rng.standard_normal(col.size).astype(np.float32)
+    return synth.Graph(rowptr, col, val, n, m)
+
+
+def _shifted(x, by):
+    """A contiguous copy of x whose first element sits `by` elements past an aligned address."""
+    import torch
+    buf = torch.empty(x.numel() + by, dtype=x.dtype, device=x.device)
+    out = buf[by:].view(x.shape)
+    out.copy_(x)
+    return out
+
+
+def _guarded(shape, dtype, by):
+    """(output view, its whole buffer): GUARD + by elements before it and GUARD after, all 7."""
+    import torch
+    n = int(np.prod(shape))
+    buf = torch.full((n + 2 * GUARD + by,), 7, dtype=dtype, device="cuda")
+    return buf[GUARD + by:GUARD + by + n].view(shape), buf
+
+
+def _untouched(buf, n, by):
+    import torch
+    assert torch.all(buf[:GUARD + by] == 7) and torch.all(buf[GUARD + by + n:] == 7), "wrote past the output"
+
+
+def _plans(cg, rp, cl, g, width, heads=0):
+    yield None
+    for kw in ({"mode": "neighbor_group", "group_size": 40}, {"mode": "neighbor_group", "group_size": 40, "col": cl,
+                                                              "n_cols": g.n_cols, "slice_min": 30}):
+        p = cg.Plan(rp, g.nnz, max_feat=width, max_heads=heads, **kw)
+        try:
+            yield p
+        finally:
+            p.close()
+
+
+@pytest.mark.parametrize("F", [4, 5, 8, 9, 15, 17, 31, 33, 41, 63, 65, 129, 257, 300, 515, 2051])
+@pytest.mark.parametrize("xk,yk", [("f32", "f32"), ("bf16", "bf16"), ("f16", "f32")])
+def test_spmm_odd_widths_and_alignment(cg, F, xk, yk):
+    import torch
+    g = _graph(F)
+    say(f"spmm F={F} {xk}->{yk}")
+    rp, cl, vl = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, F), 31 + F, xk)
+    bias = np.random.default_rng(F).standard_normal(F).astype(np.float32)
+    bd = torch.from_numpy(bias).cuda()
+    ydt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[yk]
+    Yr, Ar = oracle.spmm(g.rowptr, g.col, g.val, xh, x_dtype=xc)
+    Mr, _, Er = oracle.gspmm(g.rowptr, g.col, g.val, xh, "max", x_dtype=xc)
+    code = {"f32": oracle.F32, "bf16": oracle.BF16, "f16": oracle.F16}[yk]
+    Mr = oracle.decode(oracle.round_to(Mr, code), code).reshape(Mr.shape)
+    tol = tol_for(xk, yk)
+    for by in (0, 1, 3):
+        xs = _shifted(xd, by)
+        for plan in _plans(cg, rp, cl, g, F):
+            out, buf = _guarded((g.n_rows, F), ydt, by)
+            cg.spmm(rp, cl, vl, xs, plan=plan, out=out)
+            assert scaled_error(out, Yr, Ar) <= tol, (F, xk, by, "sum")
+            _untouched(buf, g.n_rows * F, by)
+            out, buf = _guarded((g.n_rows, F), ydt, by)
+            cg.gspmm(rp, cl, vl, xs, "mean", plan=plan, bias=bd, out=out)
+            deg = np.maximum(np.diff(g.rowptr), 1)[:, None]
+            assert scaled_error(out, Yr / deg + bias, Ar / deg + np.abs(bias)) <= tol, (F, xk, by, "mean + bias")
+            _untouched(buf, g.n_rows * F, by)
+            if yk == xk or yk == "f32":
+                out, buf = _guarded((g.n_rows, F), ydt, by)
+                arg, abuf = _guarded((g.n_rows, F), torch.int32, by)
+                cg.gspmm(rp, cl, vl, xs, "max", plan=plan, out=out, arg=arg)
+                assert np.array_equal(to_f64(out), Mr), (F, xk, by, "max")
+                assert np.array_equal(arg.cpu().numpy(), Er), (F, xk, by, "arg")
+                _untouched(buf, g.n_rows * F, by)
+                _untouched(abuf, g.n_rows * F, by)
