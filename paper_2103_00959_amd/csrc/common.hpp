@@ -186,6 +186,10 @@ __device__ __forceinline__ void store_out(T *__restrict__ p, int64_t i, const fl
 constexpr int kBufferWord3 = 0x00020000;
 // Largest buffer the 32-bit offsets of the buffer gathers address.
 constexpr uint64_t kBufferMaxBytes = 0xffffff00ull;
+// The same for gathers whose masked offset (kMaskedOffset, past every such buffer) is
+// still added to a lane's offset inside a row of at most four 16-byte vectors: the sum
+// stays past the buffer and below 2^32.
+constexpr uint32_t kMaskedOffset = 0xfff00000u;
 
 template <typename T, int VEC> struct VecBytes { static constexpr int value = (int)sizeof(T) * VEC; };
 
@@ -213,16 +217,7 @@ struct RowGather {
     __device__ __forceinline__ void load(int64_t idx, bool ok, float (&o)[VEC]) const
     {
         if constexpr (BUF) {
-            const uint32_t off = ok ? (uint32_t)idx * (uint32_t)sizeof(TX) : oob;
-            if constexpr (VecBytes<TX, VEC>::value == 16) {
-                const auto w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
-                unpack16(w[0], w[1], w[2], w[3], o);
-            } else if constexpr (sizeof(TX) == 4) {
-                o[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0));
-            } else {
-                const uint32_t h = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
-                o[0] = widen1(h);
-            }
+            load_off(ok ? (uint32_t)idx * (uint32_t)sizeof(TX) : oob, o);
         } else {
             const int64_t i = ok ? idx : 0;
             load_vec<TX, VEC>(base, i, o);
@@ -230,6 +225,21 @@ struct RowGather {
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) o[e] = 0.f;
             }
+        }
+    }
+
+    // The VEC elements at byte offset `off` (buffer gathers; zeros past the buffer).
+    __device__ __forceinline__ void load_off(uint32_t off, float (&o)[VEC]) const
+    {
+        static_assert(BUF, "buffer gathers only");
+        if constexpr (VecBytes<TX, VEC>::value == 16) {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+            unpack16(w[0], w[1], w[2], w[3], o);
+        } else if constexpr (sizeof(TX) == 4) {
+            o[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0));
+        } else {
+            const uint32_t h = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
+            o[0] = widen1(h);
         }
     }
 

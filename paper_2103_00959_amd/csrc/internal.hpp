@@ -220,7 +220,11 @@ struct RowMap {
 
 // The same with 16-byte vectors at any alignment and any width of at least one
 // vector (the kernel moves a row's last vector back to the row's end).  Rows of
-// 41 bf16 classes take 6 lanes of 8 instead of 41 element lanes of 64.
+// 41 bf16 classes take 6 lanes of 8 instead of 41 element lanes of 64.  Ragged rows
+// of 8 to 32 elements keep one element per lane (16 or 32 lanes): on 45M edges their
+// vectors measured slower (25 bf16: 1.88 against 1.73 ms, 11 fp32 1.60 against 1.41;
+// 33 bf16 2.08 against 2.81, 7 fp32 1.38 against 1.52), rows off the 64-byte grid
+// costing more requests as vectors than as lanes.
 RowMap span_map(int64_t width, int elem_bytes);
 RowMap row_map(int64_t width, int elem_bytes, int unit_elems /* vec must divide it */,
                bool aligned16);

@@ -516,7 +516,8 @@ RowMap row_map(int64_t width, int elem_bytes, int unit_elems, bool aligned16)
 RowMap span_map(int64_t width, int elem_bytes)
 {
     const int v16 = 16 / elem_bytes;
-    return lane_map(width, width >= v16 ? v16 : 1);
+    const bool ragged = width % v16 != 0 && width >= 8 && width <= 32;
+    return lane_map(width, width >= v16 && !ragged ? v16 : 1);
 }
 
 }  // namespace cogdl

@@ -174,11 +174,13 @@ cogdl_status max_reduce_launch(const char *name, const Plan &P, int64_t F, void 
 
 }  // namespace
 
-// Four features per lane, one for rows narrower than that.
+// Four features per lane for rows of whole quads and for those that one feature per
+// lane would take in several passes (more than 64); a ragged row of up to 64 is one
+// pass either way and keeps its stores apart.
 cogdl_status sum_reduce_launch(const char *name, const Plan &P, int64_t F, void *Y, int ydt,
                                bool mean, const float *bias, int act, hipStream_t s)
 {
-    if (F >= 4)
+    if (F % 4 == 0 || F > kWave)
         return reduce_launch_v<4>(name, P, F, Y, ydt, mean, bias, act, s);
     return reduce_launch_v<1>(name, P, F, Y, ydt, mean, bias, act, s);
 }
@@ -238,8 +240,11 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     a.act = act;
     const bool addop = compute == COGDL_COMPUTE_ADD || compute == COGDL_COMPUTE_SUB;
     const bool buf = a.x_bytes <= kBufferMaxBytes;
+    // sums over rows of at most four lanes: several edges of a unit side by side
+    const bool narrow = a.x_bytes <= kMaskedOffset && !maxr && !addop && m.S < 8;
     auto pick = [&](int ch) {
         return (maxr || addop) ? gspmm_pick(maxr, addop, xdt, ydt, m.vec, ch, buf)
+               : narrow        ? narrow_pick(xdt, ydt, m.vec, m.S)
                                : spmm_pick<false, false>(xdt, ydt, m.vec, ch, buf);
     };
     const int64_t units = P ? P->cap_units : out_rows;
@@ -248,7 +253,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     const bool tiny = P && m.ch == 1 && m.S >= 8;
     if (P) set_units(a, tiny ? long_units(*P) : all_units(*P));
     {
-        const int64_t upb = kBlock >> m.log2S;
+        const int64_t upb = narrow ? kBlock / 8 : kBlock >> m.log2S;
         SpmmKernel k = pick(m.ch);
         if (!k) return COGDL_ERR_DTYPE;
         int64_t blocks = (units + upb - 1) / upb;

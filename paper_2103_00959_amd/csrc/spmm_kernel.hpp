@@ -228,7 +228,138 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm(SpmmArgs a)
     }
 }
 
+// Sum of products for rows of at most four vectors (LQ = 1, 2 or 4 lanes): a group of
+// S = 8 lanes per unit takes 8 / LQ edges side by side (lane = edge slot * LQ + vector
+// of the row) and adds the slots' sums across lanes at the unit's end.  One LQ-lane
+// group per unit instead would have LQ of every 8 gather slots filled (a chunk of
+// indices is one per lane).  R chunks of 8 edges per step: R * LQ gathers in flight a
+// lane.  Bound by the rate of random lines (about 70 G/s): 45M edges, both directions,
+// 8 / 16 / 32 bf16 features 6.9 / 3.4 / 2.0 -> 1.2 / 1.3 / 1.5 ms, 2M edges
+// 0.53 / 0.28 / 0.16 -> 0.065 / 0.071 / 0.097 ms.
+template <typename TX, typename TY, int VEC, int LQ, int R>
+__global__ __launch_bounds__(kSpmmBlock) void k_spmm_narrow(SpmmArgs a)
+{
+    constexpr int S = 8, EP = S / LQ, U = LQ * R;
+    const int lane = lane_id();
+    const int lig = lane & (S - 1);
+    const int gbase = lane & ~(S - 1);
+    const int q = lig & (LQ - 1), slot = lig / LQ;
+    const UnitWalk walk = unit_walk(a.units != nullptr, a.u_lo, a.u_hi, a.lists, a.n_rows, kSpmmBlock / S,
+                                    threadIdx.x / S);
+    const int64_t stride = walk.step;
+    const int64_t hi = walk.end;
+    int64_t fe = (int64_t)q * VEC;
+    const bool act = fe < a.F;
+    if (act && fe + VEC > a.F) fe = a.F - VEC;       // the row's last vector (see k_spmm)
+    const RowGather<TX, VEC, true> X(a.X, a.x_bytes);
+    const uint32_t row_bytes = (uint32_t)a.F * (uint32_t)sizeof(TX);
+    const uint32_t lane_off = act ? (uint32_t)fe * (uint32_t)sizeof(TX) : 0u;
+    const uint32_t lane_min = act ? 0u : kMaskedOffset;
+    const auto fetch_index = [&](int k, int end, uint32_t (&o)[R], float (&v)[R]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int kc = k + r * S + lig < end ? k + r * S + lig : end - 1;
+            o[r] = (uint32_t)a.col[kc];
+            v[r] = a.val ? a.val[kc] : 1.f;
+        }
+    };
+    int64_t u = walk.first;
+    if (u >= hi) return;
+    int4 d = fetch_unit(a, u, hi);
+    uint32_t o_cur[R];
+    float v_cur[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) { o_cur[r] = 0u; v_cur[r] = 0.f; }
+    if (d.z > d.y) fetch_index(d.y, d.z, o_cur, v_cur);
+    for (;;) {
+        const int64_t un = u + stride;
+        const int4 dn = fetch_unit(a, un, hi);
+        const int row = d.x, beg = d.y, end = d.z, part = d.w;
+        float acc[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+        for (int k0 = beg; k0 < end; k0 += R * S) {
+            // row offsets of the chunk (edges past the unit: past the buffer, weight 0)
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool in = k0 + r * S + lig < end;
+                o_cur[r] = in ? o_cur[r] * row_bytes : kMaskedOffset;
+                v_cur[r] = in ? v_cur[r] : 0.f;
+            }
+            uint32_t o_nxt[R];
+            float v_nxt[R];
+            fetch_index(k0 + R * S, end, o_nxt, v_nxt);
+            float xv[U][VEC], vv[U];
+#pragma unroll
+            for (int t = 0; t < U; ++t) {
+                const int src = gbase + (t % LQ) * EP + slot;
+                const uint32_t off = (uint32_t)lane_bcast((int)o_cur[t / LQ], src) + lane_off;
+                vv[t] = lane_bcast(v_cur[t / LQ], src);
+                X.load_off(off > lane_min ? off : lane_min, xv[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < U; ++t)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vv[t], xv[t][e], acc[e]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) { o_cur[r] = o_nxt[r]; v_cur[r] = v_nxt[r]; }
+        }
+        if (dn.z > dn.y) fetch_index(dn.y, dn.z, o_cur, v_cur);
+        // the edge slots' sums: lanes with the same vector of the row
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            if constexpr (LQ == 1) acc[e] += bfly_partner<1>(acc[e]);
+            if constexpr (LQ <= 2) acc[e] += bfly_partner<2>(acc[e]);
+            acc[e] += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(acc[e]), 0x101F));   // lane ^ 4
+        }
+        if (slot == 0 && act) {
+            if (part < 0) {
+                if (a.mean && end > beg) {
+                    const float r = 1.f / (float)(end - beg);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc[e] *= r;
+                }
+                epilogue<VEC>(acc, a.bias, a.act, fe);
+                store_out<TY, VEC>(static_cast<TY *>(a.Y), (int64_t)row * a.F + fe, acc);
+            } else {
+                store_vec<float, VEC>(a.partials, (int64_t)part * a.pstride + fe, acc);
+            }
+        }
+        if (un >= hi) break;
+        u = un;
+        d = dn;
+    }
+}
+
 using SpmmKernel = void (*)(SpmmArgs);
+
+template <typename TX, typename TY>
+SpmmKernel narrow_pick_lq(int vec, int lq)
+{
+    constexpr int V = (int)(16 / sizeof(TX));
+    if (vec == 1) {
+        if (lq == 1) return k_spmm_narrow<TX, TY, 1, 1, 2>;
+        if (lq == 2) return k_spmm_narrow<TX, TY, 1, 2, 2>;
+        return k_spmm_narrow<TX, TY, 1, 4, 1>;
+    }
+    if (lq == 1) return k_spmm_narrow<TX, TY, V, 1, 2>;
+    if (lq == 2) return k_spmm_narrow<TX, TY, V, 2, 2>;
+    return k_spmm_narrow<TX, TY, V, 4, 1>;
+}
+
+// The kernel for rows on lq = 1, 2 or 4 lanes.
+inline SpmmKernel narrow_pick(int xdt, int ydt, int vec, int lq)
+{
+    const auto pick_y = [&](auto tx) -> SpmmKernel {
+        using TX = decltype(tx);
+        if (ydt == COGDL_F32) return narrow_pick_lq<TX, float>(vec, lq);
+        if (ydt == COGDL_BF16) return narrow_pick_lq<TX, bf16_t>(vec, lq);
+        return narrow_pick_lq<TX, f16_t>(vec, lq);
+    };
+    if (xdt == COGDL_F32) return pick_y(float{});
+    if (xdt == COGDL_BF16) return pick_y(bf16_t{});
+    return pick_y(f16_t{});
+}
 
 // Kernel for (VEC, CH) of one variant.  Max outputs keep the input format or
 // widen it to fp32 (each output is one fp32 message rounded once); the caller

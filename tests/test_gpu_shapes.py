@@ -67,7 +67,7 @@ def _plans(cg, rp, cl, g, width, heads=0):
             p.close()
 
 
-@pytest.mark.parametrize("F", [4, 5, 8, 9, 15, 17, 31, 33, 41, 63, 65, 129, 257, 300, 515, 2051])
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 24, 31, 32, 33, 41, 63, 65, 129, 257, 300, 515, 2051])
 @pytest.mark.parametrize("xk,yk", [("f32", "f32"), ("bf16", "bf16"), ("f16", "f32")])
 def test_spmm_odd_widths_and_alignment(cg, F, xk, yk):
     import torch
