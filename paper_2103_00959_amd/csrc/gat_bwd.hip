@@ -68,7 +68,8 @@ struct BwdArgs {
     const int4 *split_rows;     // {row, first slot, #slots, degree}
     const int32_t *n_split;
     int32_t log2S;
-    int32_t log2L;              // lanes per head (fast kernel)
+    int32_t log2L;              // lanes per head (k_bwd_rows)
+    int32_t HG;                 // heads per slab (k_bwd_rows)
 };
 
 __device__ __forceinline__ int4 fetch_bwd_unit(const BwdArgs &a, int64_t u, int64_t hi)
@@ -153,21 +154,30 @@ __device__ __forceinline__ float2 unpark_stats(float v, float slope)
 // LDS floats of a rows workgroup for whole rows' parked values, shared by its sub-groups.
 constexpr int kRowParkFloats = 4096;
 
-// Pass 1, feature-parallel: one S-lane sub-group per unit, lane = VEC
-// consecutive features, head h on lanes [h L, (h + 1) L).  Requires one
-// chunk per lane (H * D <= S * VEC) and L a power of two.  Every edge k of a
-// unit is owned by lane q = (k - beg) mod M of its head, M = min(L, U): that
-// lane alone loads the edge's alpha and source score, adds its term of c, and
-// parks its dalpha and u; the head's lanes then add up their shares of c.
-// RS (batches of U = 8 edges, L >= 8): the head's partial dot products are
-// reduce-scattered over aligned groups of 8 lanes, so lane q ends with the
-// group's sum for its own edge q mod 8 (7 exchanges for the batch instead of
-// 8 butterflies of log2 L), and L > 8 adds the groups by a butterfly.
-template <typename TX, int VEC, bool BUF, bool DOT, bool RS = false, int PK = kParkSep>
+// Pass 1, feature-parallel: one S-lane sub-group per unit, each head on L = 2^log2L
+// adjacent lanes (L a power of two, at least D / VEC), lane q of a head holding its
+// features [q VEC, (q + 1) VEC).  A head that is no whole number of vectors (RAG) ends
+// with a vector moved back to its last VEC features, whose first ones, already held by
+// the lane before, are masked to zero in both operands.  Heads past the lanes of a
+// wavefront go to further slabs (grid y, HG heads each).
+//
+// Every edge k of a unit is owned by lane q = (k - beg) mod M of its head, M = 2^LM =
+// min(L, 8): that lane alone loads the edge's alpha and source score, adds its term of
+// c, and parks its dalpha and u; the head's lanes then add up their shares of c.  The
+// partial dot products of a batch of 8 edges are reduce-scattered over aligned groups of
+// M lanes, so lane q ends with the group's sums of its own 8 / M edges (7 exchanges for
+// M = 8, 6 for M = 4, against a butterfly of log2 L levels for each edge), and L > 8
+// adds the groups by a butterfly.  Bound by the gathers (128-byte lines) and the
+// per-edge arrays.  Before, heads of fewer than 8 lanes ran the butterflies and parked in
+// memory (64.3M edges, fp32, 8 heads of 16: 8.1 -> 7.1 ms) and heads of a ragged number
+// of vectors or past one wavefront ran k_bwd_rows_any (2.5M edges, one head of 41 bf16:
+// 0.61 -> 0.10 ms; 0.86M edges, 8 heads of 51: 1.23 -> 0.14 ms).
+template <typename TX, int VEC, bool BUF, bool DOT, int LM, bool RAG, int PK = kParkSep>
 __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
 {
-    constexpr int U = VEC == 1 ? 16 : 8;
-    static_assert(!RS || U == 8, "reduce-scatter over batches of 8 edges");
+    constexpr int U = 8;
+    constexpr int M = 1 << LM;
+    constexpr int EPL = U / M;       // edges of a batch owned by a lane
     // 16-bit features stay packed: four dot2 instructions per 16-byte vector
     // instead of widening both operands to fp32 (half the registers).
     constexpr bool PACKED = sizeof(TX) == 2 && VEC == 8;
@@ -178,12 +188,25 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
     const int gbase = lane & ~(S - 1);
     const int L = 1 << a.log2L;
     const int q = lig & (L - 1);
-    const int h = lig >> a.log2L;
-    const int M = L < U ? L : U;
-    const int64_t fe = (int64_t)lig * VEC;
-    const bool act = fe < a.W;
-    const bool writer = act && q < M;
+    const int hl = lig >> a.log2L;                      // head within the slab
+    const int h = (int)blockIdx.y * a.HG + hl;
     const int H = a.H;
+    const bool hact = hl < a.HG && h < H;
+    const bool act = hact && q * VEC < a.D;
+    const int over = (RAG && act && (q + 1) * VEC > a.D) ? (q + 1) * VEC - a.D : 0;   // masked front features
+    const int64_t fe = act ? (int64_t)h * a.D + q * VEC - over : 0;
+    const bool writer = hact && q < M;
+    uint32_t keep[RAG ? 4 : 1];
+    if constexpr (RAG) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if constexpr (sizeof(TX) == 4) keep[w] = w >= over ? 0xffffffffu : 0u;
+            else keep[w] = (2 * w >= over ? 0x0000ffffu : 0u) | (2 * w + 1 >= over ? 0xffff0000u : 0u);
+    }
+    const auto mask = [&](uint4 v) {
+        if constexpr (RAG) return make_uint4(v.x & keep[0], v.y & keep[1], v.z & keep[2], v.w & keep[3]);
+        else return v;
+    };
     const UnitWalk walk = unit_walk(a.units != nullptr, a.u_lo, a.u_hi, a.lists, a.n_rows,
                                     kBlock >> log2S, threadIdx.x >> log2S);
     const int64_t stride = walk.step;
@@ -203,25 +226,25 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
         const int64_t un = u + stride;
         const int4 dn = fetch_bwd_unit(a, un, hi);
         const int row = d.x, beg = d.y, end = d.z, part = d.w;
-        // a whole row whose parked values fit this sub-group's LDS share parks them
-        // there (reduce-scatter kernels; the others keep their registers for the batch)
+        // a whole row whose parked values fit this sub-group's LDS share parks them there
         float *const lds =
-            (RS && !DOT && part < 0 && (end - beg) * H * (PK == kParkSep ? 1 : 2) <= a.park_cap) ? park_mine
-                                                                                                 : nullptr;
+            (!DOT && part < 0 && (end - beg) * a.HG * (PK == kParkSep ? 1 : 2) <= a.park_cap) ? park_mine : nullptr;
         float p[PACKED ? 1 : VEC];
         uint4 pw = make_uint4(0u, 0u, 0u, 0u);
-        if constexpr (PACKED) {
-            if (act) pw = *reinterpret_cast<const uint4 *>(P + (int64_t)row * a.W + fe);
-        } else if (act) {
-            load_vec<TX, VEC>(P, (int64_t)row * a.W + fe, p);
+        if constexpr (VEC == 1) {
+            p[0] = 0.f;
+            if (act) load_vec<TX, 1>(P, (int64_t)row * a.W + fe, p);
         } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) p[e] = 0.f;
+            if (act) {
+                const u32x4_u v = *reinterpret_cast<const u32x4_u *>(P + (int64_t)row * a.W + fe);
+                pw = mask(make_uint4(v.x, v.y, v.z, v.w));
+            }
+            if constexpr (!PACKED) RowGather<TX, VEC, BUF>::unpack16(pw.x, pw.y, pw.z, pw.w, p);
         }
-        const float sd = (!DOT && act) ? a.s_dst[(int64_t)row * H + h] : 0.f;
+        const float sd = (!DOT && hact) ? a.s_dst[(int64_t)row * H + h] : 0.f;
         // kParkStats: the row's softmax state for this lane's head
-        const float rm = (PK == kParkStats && act) ? a.row_stats[(int64_t)row * 2 * H + h] : 0.f;
-        const float rrz = (PK == kParkStats && act) ? a.row_stats[(int64_t)row * 2 * H + H + h] : 0.f;
+        const float rm = (PK == kParkStats && hact) ? a.row_stats[(int64_t)row * 2 * H + h] : 0.f;
+        const float rrz = (PK == kParkStats && hact) ? a.row_stats[(int64_t)row * 2 * H + H + h] : 0.f;
         float c = 0.f;
 
         const int last = end - 1;
@@ -229,85 +252,69 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
             const int n = (end - k0 < S) ? end - k0 : S;
             const int c_nxt = col[k0 + S + lig < last ? k0 + S + lig : last];
             for (int j = 0; j < n; j += U) {
-                int cc[U];
-                bool ok[U];
+                uint4 xw[VEC > 1 ? U : 1];
+                float x1[VEC > 1 ? 1 : U][1];
 #pragma unroll
                 for (int t = 0; t < U; ++t) {
-                    ok[t] = j + t < n;
-                    cc[t] = lane_bcast(c_cur, gbase + (ok[t] ? j + t : j));
-                }
-                float xv[PACKED ? 1 : U][VEC];
-                uint4 xw[PACKED ? U : 1];
-                float al[U], ss[U];
-                bool mine[U];
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
-                    const bool on = ok[t] && act;
-                    mine[t] = on && writer && (t & (M - 1)) == q;
-                    if constexpr (PACKED) xw[t] = X.load_raw16((int64_t)cc[t] * a.W + fe, on);
-                    else X.load((int64_t)cc[t] * a.W + fe, on, xv[t]);
-                    al[t] = 0.f;
-                    ss[t] = 0.f;
-                    if constexpr (!DOT && !RS) {
-                        if (mine[t]) {
-                            ss[t] = a.s_src[(int64_t)cc[t] * H + h];
-                            if constexpr (PK == kParkStats)
-                                al[t] = alpha_value(leaky_relu(sd + ss[t], a.slope), rm, rrz);
-                            else
-                                al[t] = a.alpha[(int64_t)(k0 + j + t) * H + h];
-                        }
-                    }
+                    const bool ok = j + t < n;
+                    const int cc = lane_bcast(c_cur, gbase + (ok ? j + t : j));
+                    if constexpr (VEC == 1) X.load((int64_t)cc * a.W + fe, ok && act, x1[t]);
+                    else xw[t] = X.load_raw16((int64_t)cc * a.W + fe, ok && act);
                 }
                 float pd[U];
 #pragma unroll
                 for (int t = 0; t < U; ++t) {
                     float s = 0.f;
-                    if constexpr (PACKED) {
-                        s = dot2_acc<TX>(xw[t].x, pw.x, s);
-                        s = dot2_acc<TX>(xw[t].y, pw.y, s);
-                        s = dot2_acc<TX>(xw[t].z, pw.z, s);
-                        s = dot2_acc<TX>(xw[t].w, pw.w, s);
+                    if constexpr (VEC == 1) {
+                        s = p[0] * x1[t][0];
                     } else {
+                        const uint4 x = mask(xw[t]);
+                        if constexpr (PACKED) {
+                            s = dot2_acc<TX>(x.x, pw.x, s);
+                            s = dot2_acc<TX>(x.y, pw.y, s);
+                            s = dot2_acc<TX>(x.z, pw.z, s);
+                            s = dot2_acc<TX>(x.w, pw.w, s);
+                        } else {
+                            float xv[VEC];
+                            RowGather<TX, VEC, BUF>::unpack16(x.x, x.y, x.z, x.w, xv);
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) s = fmaf(p[e], xv[t][e], s);
+                            for (int e = 0; e < VEC; ++e) s = fmaf(p[e], xv[e], s);
+                        }
                     }
                     pd[t] = s;
                 }
-                if constexpr (RS) {
-                    // lane q completes the dot product of edge j + (q mod 8)
-                    const int t = q & 7;
-                    float s = reduce_scatter8(pd, t);
-                    for (int off = 8; off < L; off <<= 1) s += lane_xor(s, off);
-                    const bool own = j + t < n && writer;
-                    const int64_t k = k0 + j + t;
-                    // (a cross-lane read: every lane takes part)
-                    const int cme = DOT ? 0 : lane_bcast(c_cur, gbase + j + t);
-                    if (own) {
-                        if (DOT || PK == kParkSep || a.dalpha) a.dalpha[k * H + h] = s;
-                        if constexpr (!DOT) {
-                            const float ss1 = a.s_src[(int64_t)cme * H + h];
-                            const float al1 = PK == kParkStats ? alpha_value(leaky_relu(sd + ss1, a.slope), rm, rrz)
-                                                               : a.alpha[k * H + h];
-                            c = fmaf(al1, s, c);
-                            park_edge<PK>(a, k * H + h, part >= 0, al1, s, park_value(sd + ss1, a.slope, al1),
-                                          lds, (int)(k - beg) * H + h);
+                // this lane's edges of the batch: j + (q mod M) + M r
+                float sum[EPL];
+                reduce_scatter<LM>(pd, q & (M - 1), sum);
+                if constexpr (M == 8)
+                    for (int off = 8; off < L; off <<= 1) sum[0] += lane_xor(sum[0], off);
+                // (a cross-lane read: every lane takes part; with several edges a lane their
+                // scores and weights are requested together, without branches)
+                float ss1[EPL], al1[EPL];
+                if constexpr (!DOT) {
+#pragma unroll
+                    for (int r = 0; r < EPL; ++r) {
+                        const int t = (q & (M - 1)) + M * r;
+                        const int cme = lane_bcast(c_cur, gbase + j + t);
+                        const bool own = j + t < n && writer;
+                        if (EPL > 1 || own) {
+                            ss1[r] = a.s_src[own ? (int64_t)cme * H + h : 0];
+                            if constexpr (PK != kParkStats) al1[r] = a.alpha[own ? (int64_t)(k0 + j + t) * H + h : 0];
                         }
                     }
-                    continue;
                 }
-                // complete the dot products over the head's lanes (every lane of
-                // the head ends with the same bits: each level adds the same pair)
 #pragma unroll
-                for (int t = 0; t < U; ++t) pd[t] = group_sum(pd[t], L);
-#pragma unroll
-                for (int t = 0; t < U; ++t) {
+                for (int r = 0; r < EPL; ++r) {
+                    const int t = (q & (M - 1)) + M * r;
                     const int64_t k = k0 + j + t;
-                    if (mine[t]) {
-                        if (DOT || PK == kParkSep || a.dalpha) a.dalpha[k * H + h] = pd[t];
+                    if (j + t < n && writer) {
+                        if (DOT || PK == kParkSep || a.dalpha) a.dalpha[k * H + h] = sum[r];
                         if constexpr (!DOT) {
-                            c = fmaf(al[t], pd[t], c);
-                            park_edge<PK>(a, k * H + h, part >= 0, al[t], pd[t],
-                                          park_value(sd + ss[t], a.slope, al[t]), lds, (int)(k - beg) * H + h);
+                            if constexpr (PK == kParkStats)
+                                al1[r] = alpha_value(leaky_relu(sd + ss1[r], a.slope), rm, rrz);
+                            c = fmaf(al1[r], sum[r], c);
+                            park_edge<PK>(a, k * H + h, part >= 0, al1[r], sum[r],
+                                          park_value(sd + ss1[r], a.slope, al1[r]), lds, (int)(k - beg) * a.HG + hl);
                         }
                     }
                 }
@@ -321,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
             // the head's lanes hold shares of c (owners only, the others 0)
             c = group_sum(c, L);
             if (part >= 0) {
-                if (act && q == 0) a.gstats[(int64_t)part * a.sstride + h] = c;
+                if (hact && q == 0) a.gstats[(int64_t)part * a.sstride + h] = c;
             } else {
                 // this lane's parked edges: offsets q, q + M, ... of the row
                 constexpr int R = 4;
@@ -334,7 +341,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
                             const int o = o0 + r * M;
                             const int oc = o < end - beg ? o : o0;
                             const int64_t i = ((int64_t)beg + oc) * H + h;
-                            const int li = oc * H + h;
+                            const int li = oc * a.HG + hl;
                             if constexpr (PK == kParkSep) {
                                 // dalpha from its output; u from LDS (alpha from the input)
                                 // or the record (alpha, u)
@@ -367,7 +374,7 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
                     }
                 }
                 sdt = group_sum(sdt, L);
-                if (act && q == 0) a.ds_dst[(int64_t)row * H + h] = sdt;
+                if (hact && q == 0) a.ds_dst[(int64_t)row * H + h] = sdt;
             }
         }
         if (un >= hi) break;
@@ -561,41 +568,44 @@ __global__ __launch_bounds__(kBlock) void k_split_head_sums(const int4 *__restri
 
 using BwdKernel = void (*)(BwdArgs);
 
-template <typename TX, int VEC, bool DOT, int PK>
-BwdKernel pick_rows_rs(bool buf, bool rs)
+template <typename TX, int VEC, bool BUF, bool RAG, bool DOT, int PK>
+BwdKernel pick_rows_m(int lm)
 {
-    if constexpr (VEC == 1) {
-        return buf ? k_bwd_rows<TX, 1, true, DOT, false, PK> : k_bwd_rows<TX, 1, false, DOT, false, PK>;
-    } else {
-        if (rs)
-            return buf ? k_bwd_rows<TX, VEC, true, DOT, true, PK> : k_bwd_rows<TX, VEC, false, DOT, true, PK>;
-        return buf ? k_bwd_rows<TX, VEC, true, DOT, false, PK> : k_bwd_rows<TX, VEC, false, DOT, false, PK>;
-    }
+    if (lm == 0) return k_bwd_rows<TX, VEC, BUF, DOT, 0, RAG, PK>;
+    if (lm == 1) return k_bwd_rows<TX, VEC, BUF, DOT, 1, RAG, PK>;
+    if (lm == 2) return k_bwd_rows<TX, VEC, BUF, DOT, 2, RAG, PK>;
+    return k_bwd_rows<TX, VEC, BUF, DOT, 3, RAG, PK>;
+}
+
+// The 64-bit-address kernels (X past the buffer limit, or heads below a vector) mask
+// whether or not the heads are ragged.
+template <typename TX, bool DOT, int PK>
+BwdKernel pick_rows_v(bool buf, int vec, bool rag, int lm)
+{
+    constexpr int V = (int)(16 / sizeof(TX));
+    if (vec == 1) return pick_rows_m<TX, 1, false, false, DOT, PK>(lm);
+    if (!buf) return pick_rows_m<TX, V, false, true, DOT, PK>(lm);
+    return rag ? pick_rows_m<TX, V, true, true, DOT, PK>(lm) : pick_rows_m<TX, V, true, false, DOT, PK>(lm);
 }
 
 template <bool DOT, int PK>
-BwdKernel pick_rows_t(int dt, bool buf, int vec, bool rs)
+BwdKernel pick_rows_t(int dt, bool buf, int vec, bool rag, int lm)
 {
-    if (dt == COGDL_F32) {
-        if (vec == 4) return pick_rows_rs<float, 4, DOT, PK>(buf, rs);
-        return pick_rows_rs<float, 1, DOT, PK>(buf, rs);
-    }
-    if (dt == COGDL_BF16) {
-        if (vec == 8) return pick_rows_rs<bf16_t, 8, DOT, PK>(buf, rs);
-        return pick_rows_rs<bf16_t, 1, DOT, PK>(buf, rs);
-    }
-    if (vec == 8) return pick_rows_rs<f16_t, 8, DOT, PK>(buf, rs);
-    return pick_rows_rs<f16_t, 1, DOT, PK>(buf, rs);
+    if (dt == COGDL_F32) return pick_rows_v<float, DOT, PK>(buf, vec, rag, lm);
+    if (dt == COGDL_BF16) return pick_rows_v<bf16_t, DOT, PK>(buf, vec, rag, lm);
+    return pick_rows_v<f16_t, DOT, PK>(buf, vec, rag, lm);
 }
 
-// rs: the head spans 8 or more lanes (reduce-scatter; vector kernels only);
-// pk: the parking mode (the dot-product kernels have one)
+// lm: log2 of the owner lanes per head; pk: the parking mode (the dot-product kernels
+// have one)
 template <bool DOT>
-BwdKernel pick_rows(int dt, bool buf, int vec, bool rs, int pk)
+BwdKernel pick_rows(int dt, bool buf, int vec, bool rag, int lm, int pk)
 {
-    if (DOT || pk == kParkSep) return pick_rows_t<DOT, kParkSep>(dt, buf, vec, rs);
-    if (pk == kParkPair) return pick_rows_t<DOT, kParkPair>(dt, buf, vec, rs);
-    return pick_rows_t<DOT, kParkStats>(dt, buf, vec, rs);
+    if constexpr (!DOT) {
+        if (pk == kParkPair) return pick_rows_t<false, kParkPair>(dt, buf, vec, rag, lm);
+        if (pk == kParkStats) return pick_rows_t<false, kParkStats>(dt, buf, vec, rag, lm);
+    }
+    return pick_rows_t<DOT, kParkSep>(dt, buf, vec, rag, lm);
 }
 
 template <typename TX, bool DOT, int PK>
@@ -617,9 +627,11 @@ BwdKernel pick_any_t(int xdt, int pdt)
 template <bool DOT>
 BwdKernel pick_any(int xdt, int pdt, int pk)
 {
-    if (DOT || pk == kParkSep) return pick_any_t<DOT, kParkSep>(xdt, pdt);
-    if (pk == kParkPair) return pick_any_t<DOT, kParkPair>(xdt, pdt);
-    return pick_any_t<DOT, kParkStats>(xdt, pdt);
+    if constexpr (!DOT) {
+        if (pk == kParkPair) return pick_any_t<false, kParkPair>(xdt, pdt);
+        if (pk == kParkStats) return pick_any_t<false, kParkStats>(xdt, pdt);
+    }
+    return pick_any_t<DOT, kParkSep>(xdt, pdt);
 }
 
 unsigned wave_grid(int64_t work)
@@ -630,33 +642,36 @@ unsigned wave_grid(int64_t work)
     return (unsigned)b;
 }
 
-// Pass 1 over the units of `plan` (or the rows in order): the fast kernel
-// when the shape allows it, else the general one.
+// Pass 1 over the units of `plan` (or the rows in order): heads of up to 64 vectors with
+// both operands of one format run the feature-parallel kernel, the rest the general one.
 template <bool DOT>
 cogdl_status rows_pass(BwdArgs a, const Plan *P, int xdt, int pdt, const char *name,
                        hipStream_t stream)
 {
     const int64_t units = P ? P->cap_units : a.n_rows;
-    const int xb = dtype_bytes(xdt);
+    const int v16 = 16 / dtype_bytes(xdt);
     const int pk = a.row_stats ? kParkStats : (a.dalpha && a.dscore) ? kParkSep : kParkPair;
-    const bool aligned = ((uintptr_t)a.X % 16 == 0) && ((uintptr_t)a.P % 16 == 0);
-    const RowMap m = row_map(a.W, xb, a.D, aligned);
-    const int L = a.D / m.vec;
-    const bool fast = xdt == pdt && m.ch == 1 && m.n_slabs == 1 && (L & (L - 1)) == 0;
-    if (fast) {
-        a.log2S = m.log2S;
+    const int vec = a.D >= v16 ? v16 : 1;
+    int L = next_pow2((a.D + vec - 1) / vec);
+    if (xdt == pdt && L <= kWave) {
+        // sub-groups of at least 8 lanes, so that a chunk of column indices (one per lane)
+        // fills a batch of 8 edges
+        const int hp = next_pow2(a.H);
+        while (L * hp < 8) L *= 2;
+        a.HG = L * hp <= kWave ? a.H : kWave / L;
+        const int S = L * next_pow2(a.HG);
+        const int slabs = (a.H + a.HG - 1) / a.HG;
+        a.log2S = log2i(S);
         a.log2L = log2i(L);
-        const bool rs = m.vec > 1 && L >= 8;
-        BwdKernel k = pick_rows<DOT>(xdt, a.x_bytes <= kBufferMaxBytes, m.vec, rs, pk);
-        const int64_t upb = kBlock >> m.log2S;
-        const bool park_lds = !DOT && rs;
-        a.park_cap = park_lds ? kRowParkFloats / (int)upb : 0;
-        const size_t shm = park_lds ? sizeof(float) * kRowParkFloats : 0;
+        BwdKernel k = pick_rows<DOT>(xdt, a.x_bytes <= kBufferMaxBytes, vec, a.D % vec != 0, L < 8 ? a.log2L : 3, pk);
+        const int64_t upb = kBlock / S;
+        a.park_cap = DOT ? 0 : kRowParkFloats / (int)upb;
+        const size_t shm = DOT ? 0 : sizeof(float) * kRowParkFloats;
         int64_t blocks = (units + upb - 1) / upb;
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock);
         if (blocks > res) blocks = res;
         blocks = list_grid(blocks, a.lists);
-        COGDL_LAUNCH_SHM(name, k, (unsigned)blocks, kBlock, shm, stream, a);
+        COGDL_LAUNCH_SHM(name, k, dim3((unsigned)blocks, (unsigned)slabs), kBlock, shm, stream, a);
     } else {
         BwdKernel k = pick_any<DOT>(xdt, pdt, pk);
         a.park_cap = 0;

@@ -113,6 +113,39 @@ __device__ __forceinline__ float reduce_scatter8(const float (&v)[8], int hp)
     return keep + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(send), 0x101F));
 }
 
+// The same over aligned groups of M = 2^LM lanes (1, 2, 4 or 8): lane hp of the group
+// ends with the sums of v[hp + M r] in out[r].
+template <int LM>
+__device__ __forceinline__ void reduce_scatter(const float (&v)[8], int hp, float (&out)[8 >> LM])
+{
+    if constexpr (LM == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[i] = v[i];
+    } else if constexpr (LM == 3) {
+        out[0] = reduce_scatter8(v, hp);
+    } else {
+        const bool b0 = hp & 1, b1 = hp & 2;
+        float k4[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float keep = b0 ? v[2 * i + 1] : v[2 * i];
+            const float send = b0 ? v[2 * i] : v[2 * i + 1];
+            k4[i] = keep + bfly_partner<1>(send);
+        }
+        if constexpr (LM == 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = k4[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float keep = b1 ? k4[2 * i + 1] : k4[2 * i];
+                const float send = b1 ? k4[2 * i] : k4[2 * i + 1];
+                out[i] = keep + bfly_partner<2>(send);
+            }
+        }
+    }
+}
+
 // The value of lane T of this lane's aligned group of 8 (swizzle bit mode:
 // and 0x18 keeps the group, or T picks the lane).
 template <int T>

@@ -6,7 +6,8 @@ import pytest
 import oracle
 from paper_2103_00959_amd import synth
 
-from gpu_util import features, graph_to_dev, say, scaled_error, to_f64, tol_for
+from gpu_util import TOL_F32, dev, features, graph_to_dev, say, scaled_error, to_f64, tol_for
+from test_gpu_ops import _bwd_inputs, _check_bwd
 
 pytestmark = pytest.mark.gpu
 
@@ -103,3 +104,56 @@ def test_spmm_odd_widths_and_alignment(cg, F, xk, yk):
                 assert np.array_equal(arg.cpu().numpy(), Er), (F, xk, by, "arg")
                 _untouched(buf, g.n_rows * F, by)
                 _untouched(abuf, g.n_rows * F, by)
+
+
+# one head of an odd width; heads below a vector; groups of 1, 2, 4 and 8 owner lanes; heads past one
+# wavefront (slabs, the last one part full); more heads than lanes a head; a head too wide for the map
+HEADS = [(1, 41, "bf16"), (1, 8, "bf16"), (2, 9, "f16"), (3, 17, "bf16"), (1, 5, "bf16"), (2, 3, "f32"), (4, 32, "bf16"),
+         (8, 16, "f32"), (8, 51, "bf16"), (6, 128, "bf16"), (5, 200, "f32"), (64, 2, "f32"), (11, 24, "f16"),
+         (1, 300, "f32"), (1, 513, "bf16")]
+
+
+@pytest.mark.parametrize("H,D,xk", HEADS)
+def test_head_maps_backward(cg, H, D, xk):
+    """sddmm_dot, and the backward on given weights, at the edges of the head-to-lane map."""
+    import torch
+    g = _graph(H * D)
+    W = H * D
+    say(f"backward H={H} D={D} {xk}")
+    rp, cl, _ = graph_to_dev(g)
+    sd, ss, alpha, (xh, xc, xd), (gh, gc, gd) = _bwd_inputs(g, H, D, xk, 300 + W)
+    colptr, row_t, _, perm = oracle.csr_to_csc(g.rowptr, g.col, None, g.n_cols)
+    cp_d, rt_d, pm_d, sd_d, ss_d, al_d = (dev(a) for a in (colptr, row_t, perm, sd, ss, alpha))
+    dot, dab = oracle.sddmm_dot(g.rowptr, g.col, gh.reshape(g.n_rows, W), xh.reshape(g.n_cols, W), H, D, p_dtype=gc,
+                                q_dtype=xc)
+    ref = oracle.gat_backward(g.rowptr, g.col, sd, ss, alpha, xh.reshape(g.n_cols, W), gh.reshape(g.n_rows, W), H, D,
+                              slope=0.2, x_dtype=xc, dy_dtype=gc)
+    gt = synth.Graph(colptr, row_t, None, g.n_cols, g.n_rows)
+    for by in (0, 1):
+        xs, gs = _shifted(xd, by), _shifted(gd, by)
+        for plan, plan_t in zip(_plans(cg, rp, cl, g, W, H), _plans(cg, cp_d, rt_d, gt, W, H)):
+            out, buf = _guarded((g.nnz, H), torch.float32, by)
+            cg.sddmm_dot(rp, cl, gs, xs, plan=plan, out=out)
+            assert scaled_error(out, dot, dab) <= TOL_F32, (H, D, by, "dot")
+            _untouched(buf, g.nnz * H, by)
+            dX, xbuf = _guarded((g.n_cols, H, D), torch.float32, by)
+            o = cg.gat_backward(rp, cl, cp_d, rt_d, pm_d, sd_d, ss_d, al_d, xs, gs, 0.2, plan=plan, plan_t=plan_t,
+                                out={"dX": dX})
+            _check_bwd(o, ref, (H, D, by), alpha)
+            _untouched(xbuf, g.n_cols * W, by)
+
+
+@pytest.mark.parametrize("xk", ["f32", "bf16"])
+def test_head_tail_keeps_infinities_apart(cg, xk):
+    """A ragged head's masked features: an infinity in one feature of a head gives that head's
+    dot products their infinity and leaves its neighbours' finite."""
+    import torch
+    H, D = 3, 11
+    rp, cl = dev(np.array([0, 2], np.int32)), dev(np.array([0, 1], np.int32))
+    dt = torch.float32 if xk == "f32" else torch.bfloat16
+    P = torch.ones((1, H, D), dtype=dt, device="cuda")
+    for d in range(D):
+        Q = torch.ones((2, H, D), dtype=dt, device="cuda")
+        Q[0, 1, d] = float("inf")
+        want = torch.tensor([[D, float("inf"), D], [D, D, D]], dtype=torch.float32, device="cuda")
+        assert torch.equal(cg.sddmm_dot(rp, cl, P, Q), want), d
