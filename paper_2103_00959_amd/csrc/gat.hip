@@ -696,18 +696,11 @@ cogdl_status gat_aggregate_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, con
     if (n_rows == 0) return COGDL_OK;
 
     const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)Y % 16 == 0);
-    RowMap m = row_map(W, dtype_bytes(x_dtype), D, aligned);
-    if (m.S < H) {
-        m.S = next_pow2(H);
-        m.log2S = log2i(m.S);
-        m.slab = m.S * m.ch * m.vec;
-        m.n_slabs = (int)((W + m.slab - 1) / m.slab);
-    }
-    // projected source scores: each head on L = D / VEC adjacent lanes of one chunk
-    const int hl = D / m.vec;
-    if (proj && (m.vec * dtype_bytes(x_dtype) != 16 || D % m.vec != 0 || (hl & (hl - 1)) != 0 ||
-                 hl > m.S))
-        return COGDL_ERR_INVALID;
+    const HeadMap m = head_map(H, D, dtype_bytes(x_dtype));
+    // projected source scores: each head a power of two of whole aligned vectors, up to
+    // one wavefront of them
+    const int v16 = 16 / dtype_bytes(x_dtype), hl = D / v16;
+    if (proj && (!aligned || D % v16 != 0 || (hl & (hl - 1)) != 0 || hl > kWave)) return COGDL_ERR_INVALID;
     GatArgs a{};
     a.units = P ? P->units : nullptr;
     a.n_rows = n_rows;
@@ -733,20 +726,16 @@ cogdl_status gat_aggregate_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, con
     a.pstride = P ? (P->max_feat + 7) / 8 * 8 : 0;
     a.gstats = P ? P->gstats : nullptr;
     a.sstride = P ? 2 * P->max_heads : 0;
-    a.slab = m.slab;
+    a.L = m.L;
     a.log2S = m.log2S;
     const bool buf = a.x_bytes <= kBufferMaxBytes;
     const int64_t units = P ? P->cap_units : n_rows;
-    // tiny units (the sorted tail): S/4 lanes and four chunks per lane
-    const bool tiny = P && m.ch == 1 && m.S >= 8 && m.S / 4 >= H && (!proj || hl <= m.S / 4);
+    const bool tiny = P && m.tiny && (!proj || m.L <= m.S / 4);
     if (P) set_units(a, tiny ? long_units(*P) : all_units(*P));
     {
         const int64_t upb = kBlock >> m.log2S;
-        // one chunk of 16-byte vectors with 8 lanes per head: the distributed-softmax
-        // kernel (batches of 8 edges, one edge's score per lane)
-        const bool dist = soft && m.ch == 1 && m.vec * dtype_bytes(x_dtype) == 16 && D % m.vec == 0 && hl == 8;
-        GatKernel k = proj ? gat_pick_proj(x_dtype, y_dtype, m.ch, buf, dist)
-                           : gat_pick<false>(x_dtype, y_dtype, m.vec, m.ch, buf, dist);
+        GatKernel k = proj ? gat_pick_proj(x_dtype, y_dtype, m.ch, buf, m.lm)
+                           : gat_pick<false>(x_dtype, y_dtype, m.vec, m.ch, buf, soft ? m.lm : 0);
         int64_t blocks = (units + upb - 1) / upb;
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock);
         if (blocks > res) blocks = res;
@@ -762,7 +751,7 @@ cogdl_status gat_aggregate_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, con
         set_units(b, tiny_units(*P));
         b.log2S = m.log2S - 2;
         const int64_t upb = kBlock >> b.log2S;
-        GatKernel k = proj ? gat_pick_proj(x_dtype, y_dtype, 4, buf, false)
+        GatKernel k = proj ? gat_pick_proj(x_dtype, y_dtype, 4, buf, 0)
                            : gat_pick<false>(x_dtype, y_dtype, m.vec, 4, buf);
         int64_t blocks = (units + upb - 1) / upb;
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock);

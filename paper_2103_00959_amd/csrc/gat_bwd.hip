@@ -812,14 +812,7 @@ cogdl_status gat_backward_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, cons
     if (n_cols == 0) return COGDL_OK;
 
     // pass 2 on the CSC: dX and ds_src
-    const bool aligned = ((uintptr_t)dY % 16 == 0) && ((uintptr_t)dX % 16 == 0);
-    RowMap m = row_map(W, dtype_bytes(dy_dtype), D, aligned);
-    if (m.S < H) {
-        m.S = next_pow2(H);
-        m.log2S = log2i(m.S);
-        m.slab = m.S * m.ch * m.vec;
-        m.n_slabs = (int)((W + m.slab - 1) / m.slab);
-    }
+    const HeadMap m = head_map(H, D, dtype_bytes(dy_dtype));
     GatArgs g{};
     g.units = Pc ? Pc->units : nullptr;
     g.n_rows = n_cols;
@@ -839,17 +832,15 @@ cogdl_status gat_backward_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, cons
     g.perm = perm;
     g.rec = rec;
     g.ds_out = ds_src;
-    g.slab = m.slab;
+    g.L = m.L;
     g.log2S = m.log2S;
     const bool buf = g.x_bytes <= kBufferMaxBytes;
     const int64_t units = Pc ? Pc->cap_units : n_cols;
-    const bool tiny = Pc && m.ch == 1 && m.S >= 8 && m.S / 4 >= H;
+    const bool tiny = Pc && m.tiny;
     if (Pc) set_units(g, tiny ? long_units(*Pc) : all_units(*Pc));
     {
         const int64_t upb = kBlock >> m.log2S;
-        // one edge's record per lane when a head is exactly eight 16-byte vectors
-        const bool dist = m.ch == 1 && m.vec * dtype_bytes(dy_dtype) == 16 && D == 8 * m.vec;
-        GatKernel k = gat_pick<true>((int)dy_dtype, (int)dx_dtype, m.vec, m.ch, buf, dist);
+        GatKernel k = gat_pick<true>((int)dy_dtype, (int)dx_dtype, m.vec, m.ch, buf, m.lm);
         int64_t blocks = (units + upb - 1) / upb;
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock);
         if (blocks > res) blocks = res;

@@ -42,7 +42,7 @@ struct GatArgs {
     const float *a_src;         // PROJ: the source score is X[j, h, :] . a_src[h, :] (H x D fp32)
     int32_t park_cap;           // alpha wanted: LDS floats per sub-group for parked scores (0: none)
     int32_t sstride;            // 2 * max_heads
-    int32_t slab;
+    int32_t L;                  // slots (lane-chunks) per head, at least D / VEC
     int32_t log2S;
 };
 
@@ -146,12 +146,25 @@ __device__ __forceinline__ void reduce_scatter(const float (&v)[8], int hp, floa
     }
 }
 
-// The value of lane T of this lane's aligned group of 8 (swizzle bit mode:
-// and 0x18 keeps the group, or T picks the lane).
-template <int T>
-__device__ __forceinline__ float from_group8(float v)
+// The value of lane T of this lane's aligned group of 2^LM lanes: a DPP quad permute for
+// groups of 2 and 4, for 8 a swizzle (bit mode: and 0x18 keeps the group, or T picks the
+// lane).
+template <int LM, int T>
+__device__ __forceinline__ float from_group(float v)
 {
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x18 | (T << 5)));
+    if constexpr (LM == 3) return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x18 | (T << 5)));
+    constexpr int quad = LM == 2 ? T * 0x55 : (T | T << 2 | (2 + T) << 4 | (2 + T) << 6);
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, quad, 0xF, 0xF, false));
+}
+
+// w[t], t = 0 .. 7: the weight of edge t of a batch, held by lane t mod 2^LM of the group
+// as its element t >> LM.
+template <int LM, int T = 0>
+__device__ __forceinline__ void share_weights(const float (&own)[8 >> LM], float (&w)[8])
+{
+    w[T] = from_group<LM, (T & ((1 << LM) - 1))>(own[T >> LM]);
+    if constexpr (T < 7) share_weights<LM, T + 1>(own, w);
 }
 
 // PM (source-score mode): 0 and 3 read s_src (or, BWD / alpha_in, the given
@@ -163,23 +176,28 @@ __device__ __forceinline__ float from_group8(float v)
 // from s_src: a GAT layer's source score is that projection, and the random
 // 4H-byte score row of each edge costs a whole cache line.  Needs 16-byte
 // vectors, L a power of two and each head inside one chunk (the host checks).
-// PM = 2 (one chunk, L equal to the U edges of a batch): the partial products
-// are reduce-scattered over the head's lanes instead, so each lane ends with
-// the score of one edge of the batch and does that edge's softmax arithmetic
-// alone (LeakyReLU, exp, its share of z; the batch maximum by a butterfly),
-// and the weights are handed back to the head's lanes by swizzles: the
-// per-edge scalar work of the softmax is done once per head instead of once
-// per lane of the head.  PM = 3 is the same distribution with the scores read
-// from s_src: each lane reads the score of its own edge only.  BWD with PM = 3:
-// each lane reads the (weight, value) record of its own edge of the batch, the
-// weights reach the head's lanes by swizzles and each lane sums the values of
-// its own edges, added over the head at the unit's end.
+// PM = 2 (one chunk, L a power of two, at least 2): the partial products are
+// reduce-scattered over groups of M = 2^LM = min(L, 8) of the head's lanes instead, so
+// each lane ends with the scores of 8 / M edges of the batch and does those edges'
+// softmax arithmetic alone (LeakyReLU, exp, their share of z; the batch maximum by a
+// butterfly), and the weights are handed back to the head's lanes by lane moves: the
+// per-edge scalar work of the softmax is done once per group instead of once per lane of
+// the head.  PM = 3 is the same distribution with the scores read from s_src: each lane
+// reads the scores of its own edges only.  BWD with PM = 3: each lane reads the (weight,
+// value) records of its own edges of the batch, the weights reach the head's lanes by
+// lane moves and each lane sums the values of its own edges, added over the group at the
+// unit's end.  Lanes of a head past its last vector take part in the scores only.
+// Where the table is cached the kernels are bound by their vector ALU work, which the
+// sharing cuts; elsewhere by the lines they gather.  Against every lane of a head doing
+// every edge (and element lanes for ragged heads): projected, 4 heads of 32 bf16 on
+// 114.6M edges 2.45 -> 2.02 ms; one head of 48 there 1.57 -> 1.18 ms; one head of 41 on
+// 2.5M edges 0.20 -> 0.08 ms, its backward on the CSC 0.23 -> 0.10 ms.
 // The forward's four-chunk kernel with given scores and packed 16-bit rows runs
 // three wavefronts per SIMD (a few registers spilled, still faster than two).
 template <int VEC, int CH, bool BUF, bool BWD, int PM, int XB>
 constexpr bool gat_given_packed = BUF && !BWD && PM == 0 && CH == 4 && VEC == 8 && XB == 2;
 
-template <typename TX, typename TY, int VEC, int CH, bool BUF, bool BWD, int PM = 0>
+template <typename TX, typename TY, int VEC, int CH, bool BUF, bool BWD, int PM = 0, int LM = 0>
 __global__ __launch_bounds__(kGatBlock, ((CH == 1 && BUF && !BWD)                                   ? 4
                                          : (gat_given_packed<VEC, CH, BUF, BWD, PM, (int)sizeof(TX)>) ? 3
                                                                                                       : 1))
@@ -188,7 +206,8 @@ void k_gat(GatArgs a)
     constexpr bool PROJ = PM == 1 || PM == 2;
     constexpr bool DIST = PM == 2 || PM == 3;
     static_assert(!BWD || PM == 0 || PM == 3, "the backward reads its weights");
-    constexpr int U = (VEC == 1 ? 16 : 8) / CH;
+    constexpr int U = 8 / CH;
+    constexpr int M = 1 << LM, EPL = DIST ? 8 >> LM : 1;    // DIST: group lanes, edges a lane owns
     const int log2S = a.log2S;
     const int S = 1 << log2S;
     const int lane = lane_id();
@@ -201,16 +220,23 @@ void k_gat(GatArgs a)
     const int64_t stride = walk.step;
     const int64_t hi = walk.end;
 
-    const int64_t f0 = (int64_t)blockIdx.y * a.slab;
-    const int64_t f_end = (f0 + a.slab < a.W) ? f0 + a.slab : a.W;
+    // Slot s (a lane's chunk c of a slab: s = slab + c S + lane) holds vector s mod L of head
+    // s / L; a head's last vector, when ragged, moves back to its last VEC features (the
+    // overlap is summed in the same order and stored with the same bits).
+    const int slot0 = (int)blockIdx.y * CH * S;
     int64_t fe[CH];
-    bool act[CH];
+    bool act[CH], first[CH];        // holds features; holds the head's first ones
     int hd[CH];
+    bool hact = false;              // chunk 0 belongs to a head
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        fe[c] = f0 + (int64_t)(c * S + lig) * VEC;
-        act[c] = fe[c] < f_end;
-        hd[c] = act[c] ? (int)(fe[c] / a.D) : 0;
+        const int s = slot0 + c * S + lig;
+        const int h = s / a.L, f = (s - h * a.L) * VEC;
+        if (c == 0) hact = h < H;
+        act[c] = h < H && f < a.D;
+        first[c] = act[c] && f == 0;
+        hd[c] = h < H ? h : 0;
+        fe[c] = act[c] ? (int64_t)h * a.D + (f + VEC <= a.D ? f : a.D - VEC) : 0;
     }
     const RowGather<TX, VEC, BUF> X(a.X, a.x_bytes);
     const int32_t *__restrict__ col = a.col;
@@ -223,9 +249,14 @@ void k_gat(GatArgs a)
     constexpr int kAsrcMax = kWave * CH * VEC;          // a slab's width at most
     __shared__ float asrc_lds[ASRC_LDS ? kAsrcMax : 1];
     float asrc[PROJ && !ASRC_LDS ? CH : 1][PROJ && !ASRC_LDS ? VEC : 1];
-    const int hl = PROJ ? a.D / VEC : 1;
+    const int hl = PROJ ? a.L : 1;
     if constexpr (ASRC_LDS) {
-        for (int64_t f = threadIdx.x; f < f_end - f0; f += kGatBlock) asrc_lds[f] = a.a_src[f0 + f];
+        // slot s of the slab at s VEC, zeros where it holds no feature
+        for (int i = threadIdx.x; i < CH * S * VEC; i += kGatBlock) {
+            const int s = slot0 + i / VEC;
+            const int h = s / a.L, f = (s - h * a.L) * VEC + i % VEC;
+            asrc_lds[i] = (h < H && f < a.D) ? a.a_src[(int64_t)h * a.D + f] : 0.f;
+        }
         __syncthreads();
     } else if constexpr (PROJ) {
 #pragma unroll
@@ -241,6 +272,7 @@ void k_gat(GatArgs a)
 #define COGDL_PARK_LDS (a.park_cap > 0 && part < 0 && (end - beg) * H <= a.park_cap)
 #define COGDL_LDS_PARK (park_buf + (threadIdx.x >> log2S) * a.park_cap)
     const int q_slot = lig / H, q_head = lig % H;
+    const int lane_of_head = DIST ? lig & (a.L - 1) : 0;
 
     // Resident grid, software-pipelined over units as in the SpMM kernel.
     int64_t u = walk.first;
@@ -313,67 +345,75 @@ void k_gat(GatArgs a)
                         if constexpr (XPACK) xw[t][c] = X.load_raw16((int64_t)cc[t] * a.W + fe[c], on);
                         else X.load((int64_t)cc[t] * a.W + fe[c], on, xv[t][c]);
                     }
-                if constexpr (DIST && BWD) {
+                if constexpr (DIST) {
                     static_assert(CH == 1 && U == 8, "one chunk, batches of 8 edges");
-                    const int hp = lig & (U - 1);
-                    const bool mine = j + hp < n && act[0];
-                    const int pme = lane_bcast(p_cur, gbase + j + hp);
-                    const float2 r = a.rec[mine ? (int64_t)pme * H + hd[0] : 0];
-                    dsum[0] += mine ? r.y : 0.f;
-                    const float wv = mine ? r.x : 0.f;
-                    float wt[U];
-                    wt[0] = from_group8<0>(wv); wt[1] = from_group8<1>(wv);
-                    wt[2] = from_group8<2>(wv); wt[3] = from_group8<3>(wv);
-                    wt[4] = from_group8<4>(wv); wt[5] = from_group8<5>(wv);
-                    wt[6] = from_group8<6>(wv); wt[7] = from_group8<7>(wv);
+                    const int hp = lig & (M - 1);
+                    float own[EPL];                       // weights of this lane's edges hp + M r of the batch
+                    if constexpr (BWD) {
 #pragma unroll
-                    for (int t = 0; t < U; ++t)
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) acc[0][e] = fmaf(wt[t], xv[t][0][e], acc[0][e]);
-                    continue;
-                } else if constexpr (DIST) {
-                    static_assert(CH == 1 && U == 8, "one chunk, batches of 8 edges");
-                    const int hp = lig & (U - 1);
-                    const bool mine = j + hp < n && act[0];       // this lane's edge of the batch
-                    float sc;
-                    if constexpr (PROJ) {
-                        float pp[U];
-#pragma unroll
-                        for (int t = 0; t < U; ++t) {
-                            float p = 0.f;
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) p = fmaf(xv[t][0][e], asrc[0][e], p);
-                            pp[t] = p;
+                        for (int r = 0; r < EPL; ++r) {
+                            const int t = hp + M * r;
+                            const bool mine = j + t < n && hact;
+                            const int pme = lane_bcast(p_cur, gbase + j + t);
+                            const float2 v = a.rec[mine ? (int64_t)pme * H + hd[0] : 0];
+                            dsum[0] += mine ? v.y : 0.f;
+                            own[r] = mine ? v.x : 0.f;
                         }
-                        sc = reduce_scatter8(pp, hp);
                     } else {
-                        const int cme = lane_bcast(c_cur, gbase + j + hp);
-                        sc = wsrc[mine ? (int64_t)cme * H + hd[0] : 0];
-                    }
-                    const float e1 = mine ? leaky_relu(sd[0] + sc, a.slope) : -INFINITY;
-                    if constexpr (!PROJ) {
-                        // alpha wanted: each lane parks the score of its own edge
-                        if (a.alpha_out != nullptr && mine) {
-                            const int k = k0 + j + hp;
-                            if (COGDL_PARK_LDS) COGDL_LDS_PARK[(k - beg) * H + hd[0]] = e1;
-                            else a.alpha_out[(int64_t)k * H + hd[0]] = e1;
+                        float sc[EPL];
+                        if constexpr (PROJ) {
+                            float pp[U];
+#pragma unroll
+                            for (int t = 0; t < U; ++t) {
+                                float p = 0.f;
+#pragma unroll
+                                for (int e = 0; e < VEC; ++e) p = fmaf(xv[t][0][e], asrc[0][e], p);
+                                pp[t] = p;
+                            }
+                            reduce_scatter<LM>(pp, hp, sc);
+                            if constexpr (M == 8)
+                                for (int off = 8; off < hl; off <<= 1) sc[0] += lane_xor(sc[0], off);
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < EPL; ++r) {
+                                const int t = hp + M * r;
+                                const int cme = lane_bcast(c_cur, gbase + j + t);
+                                sc[r] = wsrc[j + t < n && hact ? (int64_t)cme * H + hd[0] : 0];
+                            }
+                        }
+                        float mb = m[0];
+#pragma unroll
+                        for (int r = 0; r < EPL; ++r) {
+                            const bool mine = j + hp + M * r < n && hact;
+                            sc[r] = mine ? leaky_relu(sd[0] + sc[r], a.slope) : -INFINITY;
+                            if constexpr (!PROJ) {
+                                // alpha wanted: each lane parks the scores of its own edges (of a
+                                // head on more than M lanes, the first group's lanes)
+                                if (a.alpha_out != nullptr && mine && lane_of_head < M) {
+                                    const int k = k0 + j + hp + M * r;
+                                    if (COGDL_PARK_LDS) COGDL_LDS_PARK[(k - beg) * H + hd[0]] = sc[r];
+                                    else a.alpha_out[(int64_t)k * H + hd[0]] = sc[r];
+                                }
+                            }
+                            mb = fmaxf(mb, sc[r]);
+                        }
+                        mb = group_reduce(mb, M, [](float x, float y) { return fmaxf(x, y); });
+                        if (mb > m[0]) {
+                            const float r = __expf(m[0] - mb);
+                            z[0] *= r;
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) acc[0][e] *= r;
+                            m[0] = mb;
+                        }
+                        const float ml = m[0] * kLog2eF;
+#pragma unroll
+                        for (int r = 0; r < EPL; ++r) {
+                            own[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], kLog2eF, -ml));
+                            z[0] += own[r];    // this lane's share of z, summed over the group at the unit's end
                         }
                     }
-                    const float mb = fmaxf(m[0], group_reduce(e1, U, [](float x, float y) { return fmaxf(x, y); }));
-                    if (mb > m[0]) {
-                        const float r = __expf(m[0] - mb);
-                        z[0] *= r;
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) acc[0][e] *= r;
-                        m[0] = mb;
-                    }
-                    const float pl = __builtin_amdgcn_exp2f(fmaf(e1, kLog2eF, -m[0] * kLog2eF));
-                    z[0] += pl;            // this lane's share of z, summed over the head at the unit's end
                     float wt[U];
-                    wt[0] = from_group8<0>(pl); wt[1] = from_group8<1>(pl);
-                    wt[2] = from_group8<2>(pl); wt[3] = from_group8<3>(pl);
-                    wt[4] = from_group8<4>(pl); wt[5] = from_group8<5>(pl);
-                    wt[6] = from_group8<6>(pl); wt[7] = from_group8<7>(pl);
+                    share_weights<LM>(own, wt);
 #pragma unroll
                     for (int t = 0; t < U; ++t)
 #pragma unroll
@@ -387,7 +427,7 @@ void k_gat(GatArgs a)
                     for (int c = 0; c < CH; ++c) {
                         float as[VEC];
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) as[e] = asrc_lds[fe[c] - f0 + e];
+                        for (int e = 0; e < VEC; ++e) as[e] = asrc_lds[(c * S + lig) * VEC + e];
 #pragma unroll
                         for (int t = 0; t < U; ++t) {
                             float xe[VEC];
@@ -427,7 +467,7 @@ void k_gat(GatArgs a)
                         // alpha wanted: park the raw scores, one lane per head and edge
                         // (the lane of the head's first feature in this slab)
                         if constexpr (!PROJ) {
-                            if (a.alpha_out != nullptr && act[c] && fe[c] % a.D == 0) {
+                            if (a.alpha_out != nullptr && first[c]) {
 #pragma unroll
                                 for (int t = 0; t < U; ++t) {
                                     if (!ok[t]) continue;
@@ -485,8 +525,8 @@ void k_gat(GatArgs a)
             c_cur = c_nxt;
             if constexpr (BWD) p_cur = p_nxt;
         }
-        if constexpr (DIST && BWD) dsum[0] = group_sum(dsum[0], U);   // the head's shares
-        else if constexpr (DIST) z[0] = group_sum(z[0], U);          // the head's shares of z
+        if constexpr (DIST && BWD) dsum[0] = group_sum(dsum[0], M);   // the group's shares
+        else if constexpr (DIST) z[0] = group_sum(z[0], M);          // (of z)
         int c_first_next = 0, p_first_next = 0;
         if (dn.z > dn.y) {
             const int k = dn.y + lig < dn.z - 1 ? dn.y + lig : dn.z - 1;
@@ -497,7 +537,7 @@ void k_gat(GatArgs a)
             // the per-head sum, written once by the lane holding the head's first feature
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                if (!act[c] || fe[c] % a.D != 0) continue;
+                if (!first[c]) continue;
                 if (part >= 0) a.gstats[(int64_t)part * a.sstride + hd[c]] = dsum[c];
                 else a.ds_out[(int64_t)row * H + hd[c]] = dsum[c];
             }
@@ -509,7 +549,7 @@ void k_gat(GatArgs a)
             for (int c = 0; c < CH; ++c) {
                 if (!act[c]) continue;
                 store_vec<float, VEC>(a.partials, (int64_t)part * a.pstride + fe[c], acc[c]);
-                if (soft && fe[c] % a.D == 0) {
+                if (soft && first[c]) {
                     a.gstats[(int64_t)part * a.sstride + hd[c]] = m[c];
                     a.gstats[(int64_t)part * a.sstride + (a.sstride >> 1) + hd[c]] = z[c];
                 }
@@ -521,7 +561,7 @@ void k_gat(GatArgs a)
                 rz[c] = (soft && z[c] > 0.f) ? 1.f / z[c] : 1.f;
                 // the row's softmax state, from which alpha = alpha_value(e, m, 1/z) can be
                 // rebuilt (every lane of the head holds it; the lane of its first feature writes)
-                if (soft && a.row_stats != nullptr && act[c] && fe[c] % a.D == 0) {
+                if (soft && a.row_stats != nullptr && first[c]) {
                     a.row_stats[(int64_t)row * 2 * H + hd[c]] = m[c];
                     a.row_stats[(int64_t)row * 2 * H + H + hd[c]] = rz[c];
                 }
@@ -542,9 +582,9 @@ void k_gat(GatArgs a)
                 // of h in this slab.
                 const int h1 = q_head;
                 const int slot = q_slot;
-                const int64_t hf = (int64_t)h1 * a.D;
-                const bool mine_head = hf >= f0 && hf < f_end;
-                const int idx = mine_head ? (int)((hf - f0) / VEC) : 0;
+                const int hs = h1 * a.L - slot0;
+                const bool mine_head = hs >= 0 && hs < CH * S;
+                const int idx = mine_head ? hs : 0;
                 const int src_c = idx / S, src_l = idx % S;
                 float m1 = 0.f, r1 = 0.f;
 #pragma unroll
@@ -577,49 +617,50 @@ void k_gat(GatArgs a)
 
 using GatKernel = void (*)(GatArgs);
 
-template <typename TX, typename TY, bool BUF, bool BWD>
-GatKernel gat_pick_vec(int vec, int ch, bool dist)
+// lm: log2 of the lanes that share a batch's scores (PM = 3: one chunk, a power of two of
+// slots per head), 0 for none.  The 64-bit-address kernels share over 8 lanes or not at all.
+template <typename TX, typename TY, int VEC, bool BUF, bool BWD>
+GatKernel gat_pick_vec(int ch, int lm)
 {
-    constexpr int V = (int)(16 / sizeof(TX));
-    if (vec == 1) {
-        if (ch == 1) return k_gat<TX, TY, 1, 1, BUF, BWD>;
-        if (ch == 2) return k_gat<TX, TY, 1, 2, BUF, BWD>;
-        return k_gat<TX, TY, 1, 4, BUF, BWD>;
+    if constexpr (BUF) {
+        if (ch == 1 && lm == 1) return k_gat<TX, TY, VEC, 1, BUF, BWD, 3, 1>;
+        if (ch == 1 && lm == 2) return k_gat<TX, TY, VEC, 1, BUF, BWD, 3, 2>;
     }
-    if (ch == 1) {
-        if (dist) return k_gat<TX, TY, V, 1, BUF, BWD, 3>;
-        return k_gat<TX, TY, V, 1, BUF, BWD>;
-    }
-    if (ch == 2) return k_gat<TX, TY, V, 2, BUF, BWD>;
-    return k_gat<TX, TY, V, 4, BUF, BWD>;
+    if (ch == 1 && lm == 3) return k_gat<TX, TY, VEC, 1, BUF, BWD, 3, 3>;
+    if (ch == 1) return k_gat<TX, TY, VEC, 1, BUF, BWD>;
+    if (ch == 2) return k_gat<TX, TY, VEC, 2, BUF, BWD>;
+    return k_gat<TX, TY, VEC, 4, BUF, BWD>;
 }
 
 template <typename TX, bool BUF, bool BWD>
-GatKernel gat_pick_y(int ydt, int vec, int ch, bool dist)
+GatKernel gat_pick_y(int ydt, int vec, int ch, int lm)
 {
-    if (ydt == COGDL_F32) return gat_pick_vec<TX, float, BUF, BWD>(vec, ch, dist);
-    if (ydt == COGDL_BF16) return gat_pick_vec<TX, bf16_t, BUF, BWD>(vec, ch, dist);
-    return gat_pick_vec<TX, f16_t, BUF, BWD>(vec, ch, dist);
+    constexpr int V = (int)(16 / sizeof(TX));
+    if (vec == 1) {
+        if (ydt == COGDL_F32) return gat_pick_vec<TX, float, 1, BUF, BWD>(ch, lm);
+        if (ydt == COGDL_BF16) return gat_pick_vec<TX, bf16_t, 1, BUF, BWD>(ch, lm);
+        return gat_pick_vec<TX, f16_t, 1, BUF, BWD>(ch, lm);
+    }
+    if (ydt == COGDL_F32) return gat_pick_vec<TX, float, V, BUF, BWD>(ch, lm);
+    if (ydt == COGDL_BF16) return gat_pick_vec<TX, bf16_t, V, BUF, BWD>(ch, lm);
+    return gat_pick_vec<TX, f16_t, V, BUF, BWD>(ch, lm);
 }
 
-// dist: the distributed kernel (PM = 3: scores read from s_src, or BWD's
-// records, one edge per lane; one chunk of 16-byte vectors, 8 lanes per head).
 template <bool BWD>
-GatKernel gat_pick(int xdt, int ydt, int vec, int ch, bool buf, bool dist = false)
+GatKernel gat_pick(int xdt, int ydt, int vec, int ch, bool buf, int lm = 0)
 {
     if (buf) {
-        if (xdt == COGDL_F32) return gat_pick_y<float, true, BWD>(ydt, vec, ch, dist);
-        if (xdt == COGDL_BF16) return gat_pick_y<bf16_t, true, BWD>(ydt, vec, ch, dist);
-        return gat_pick_y<f16_t, true, BWD>(ydt, vec, ch, dist);
+        if (xdt == COGDL_F32) return gat_pick_y<float, true, BWD>(ydt, vec, ch, lm);
+        if (xdt == COGDL_BF16) return gat_pick_y<bf16_t, true, BWD>(ydt, vec, ch, lm);
+        return gat_pick_y<f16_t, true, BWD>(ydt, vec, ch, lm);
     }
-    if (xdt == COGDL_F32) return gat_pick_y<float, false, BWD>(ydt, vec, ch, dist);
-    if (xdt == COGDL_BF16) return gat_pick_y<bf16_t, false, BWD>(ydt, vec, ch, dist);
-    return gat_pick_y<f16_t, false, BWD>(ydt, vec, ch, dist);
+    if (xdt == COGDL_F32) return gat_pick_y<float, false, BWD>(ydt, vec, ch, lm);
+    if (xdt == COGDL_BF16) return gat_pick_y<bf16_t, false, BWD>(ydt, vec, ch, lm);
+    return gat_pick_y<f16_t, false, BWD>(ydt, vec, ch, lm);
 }
 
 // The forward kernels with projected source scores (16-byte vectors only),
-// instantiated in gat_proj.hip; dist: the distributed-softmax mode (one chunk,
-// 8 lanes per head).
-GatKernel gat_pick_proj(int xdt, int ydt, int ch, bool buf, bool dist);
+// instantiated in gat_proj.hip; lm as gat_pick's (PM = 2).
+GatKernel gat_pick_proj(int xdt, int ydt, int ch, bool buf, int lm);
 
 }  // namespace cogdl

@@ -206,8 +206,7 @@ inline int log2i(int v)
     return l;
 }
 
-// Launch geometry of the gather kernels for one row of `width` elements of a
-// `bytes`-wide format: VEC elements per lane, S lanes per edge row, CH chunks
+// Launch geometry of the SpMM gather kernels for one row of `width` elements: VEC elements per lane, S lanes per edge row, CH chunks
 // per lane and the number of feature slabs.
 struct RowMap {
     int vec = 1;
@@ -218,16 +217,33 @@ struct RowMap {
     int n_slabs = 1;
 };
 
-// The same with 16-byte vectors at any alignment and any width of at least one
-// vector (the kernel moves a row's last vector back to the row's end).  Rows of
+// 16-byte vectors at any alignment and any width of at least one vector (the kernel
+// moves a row's last vector back to the row's end).  Rows of
 // 41 bf16 classes take 6 lanes of 8 instead of 41 element lanes of 64.  Ragged rows
 // of 8 to 32 elements keep one element per lane (16 or 32 lanes): on 45M edges their
 // vectors measured slower (25 bf16: 1.88 against 1.73 ms, 11 fp32 1.60 against 1.41;
 // 33 bf16 2.08 against 2.81, 7 fp32 1.38 against 1.52), rows off the 64-byte grid
 // costing more requests as vectors than as lanes.
 RowMap span_map(int64_t width, int elem_bytes);
-RowMap row_map(int64_t width, int elem_bytes, int unit_elems /* vec must divide it */,
-               bool aligned16);
+
+// Geometry of k_gat for H heads of D features: 16-byte vectors at any alignment (one
+// element per lane for heads narrower than a vector), L slots per head (k_gat), S lanes
+// per edge row, CH slots per lane, and lm = log2 of the lanes of a head that share a
+// batch's scores.  L is the head's vectors rounded up to a power of two wherever that
+// needs no more lanes (always for a power of two of heads), at least so many that S >= 8:
+// a chunk of column indices, one per lane, then fills a batch of 8 edges.
+struct HeadMap {
+    int vec = 1;
+    int L = 1;
+    int S = 64;
+    int log2S = 6;
+    int ch = 1;
+    int lm = 0;
+    int n_slabs = 1;
+    bool tiny = false;     // tiny units on S / 4 lanes, four slots a lane
+};
+
+HeadMap head_map(int H, int D, int elem_bytes);
 
 }  // namespace cogdl
 

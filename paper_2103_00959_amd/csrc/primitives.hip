@@ -507,17 +507,38 @@ RowMap lane_map(int64_t width, int vec)
 
 }  // namespace
 
-RowMap row_map(int64_t width, int elem_bytes, int unit_elems, bool aligned16)
-{
-    const int v16 = 16 / elem_bytes;
-    return lane_map(width, (aligned16 && width % v16 == 0 && unit_elems % v16 == 0) ? v16 : 1);
-}
-
 RowMap span_map(int64_t width, int elem_bytes)
 {
     const int v16 = 16 / elem_bytes;
     const bool ragged = width % v16 != 0 && width >= 8 && width <= 32;
     return lane_map(width, width >= v16 && !ragged ? v16 : 1);
+}
+
+HeadMap head_map(int H, int D, int elem_bytes)
+{
+    HeadMap m;
+    const int v16 = 16 / elem_bytes;
+    m.vec = D >= v16 ? v16 : 1;
+    const int vecs = (D + m.vec - 1) / m.vec;
+    const int64_t slots = (int64_t)H * vecs;
+    m.L = vecs;
+    if (slots <= kWave) {
+        const int fit = next_pow2((int)slots) < 8 ? 8 : next_pow2((int)slots);
+        const int heads = next_pow2(H);
+        int L = next_pow2(vecs);
+        while (L * heads < 8) L *= 2;
+        if (L * heads <= fit) m.L = L;
+        m.S = fit;
+        if ((m.L & (m.L - 1)) == 0) m.lm = log2i(m.L < 8 ? m.L : 8);
+    } else {
+        const int64_t ch = (slots + kWave - 1) / kWave;
+        m.S = kWave;
+        m.ch = ch <= 2 ? 2 : 4;
+        m.n_slabs = (int)((slots + (int64_t)m.S * m.ch - 1) / ((int64_t)m.S * m.ch));
+    }
+    m.log2S = log2i(m.S);
+    m.tiny = m.ch == 1 && m.S / 4 >= H && (m.S >= 16 || m.lm == 0);
+    return m;
 }
 
 }  // namespace cogdl

@@ -6,7 +6,8 @@ import pytest
 import oracle
 from paper_2103_00959_amd import synth
 
-from gpu_util import TOL_F32, dev, features, graph_to_dev, say, scaled_error, to_f64, tol_for
+from gpu_util import (TOL_ALPHA, TOL_F32, alpha_bound_scale, alpha_close, dev, features, graph_to_dev, say, scaled_error,
+                      to_f64, tol_for)
 from test_gpu_ops import _bwd_inputs, _check_bwd
 
 pytestmark = pytest.mark.gpu
@@ -157,3 +158,84 @@ def test_head_tail_keeps_infinities_apart(cg, xk):
         Q[0, 1, d] = float("inf")
         want = torch.tensor([[D, float("inf"), D], [D, D, D]], dtype=torch.float32, device="cuda")
         assert torch.equal(cg.sddmm_dot(rp, cl, P, Q), want), d
+
+
+def _alpha_ok(alpha, g, sd, ss):
+    ref = oracle.edge_softmax(g.rowptr, g.col, sd, ss, slope=0.2)
+    scale = np.asarray(alpha_bound_scale(g.rowptr, g.col, sd, ss)).reshape(ref.shape)
+    return alpha_close(alpha, ref, scale) <= TOL_ALPHA
+
+
+@pytest.mark.parametrize("H,D,xk", HEADS)
+def test_head_maps_forward(cg, H, D, xk):
+    """The aggregation with and without alpha out, on given weights, with bias and ELU, and
+    through row states with the backward that rebuilds the weights, at the same head shapes."""
+    import torch
+    g = _graph(H * D + 1)
+    W = H * D
+    say(f"forward H={H} D={D} {xk}")
+    rp, cl, _ = graph_to_dev(g)
+    sd, ss, alpha, (xh, xc, xd), (gh, gc, gd) = _bwd_inputs(g, H, D, xk, 700 + W)
+    sd_d, ss_d, al_d = dev(sd), dev(ss), dev(alpha)
+    colptr, row_t, _, perm = oracle.csr_to_csc(g.rowptr, g.col, None, g.n_cols)
+    cp_d, rt_d, pm_d = dev(colptr), dev(row_t), dev(perm)
+    gt = synth.Graph(colptr, row_t, None, g.n_cols, g.n_rows)
+    Yr, Ar = oracle.gat(g.rowptr, g.col, sd, ss, xh.reshape(g.n_cols, W), H, D, slope=0.2, x_dtype=xc)
+    bias = np.random.default_rng(W).standard_normal(W).astype(np.float32)
+    Yb = Yr + bias
+    Yb = np.where(Yb > 0, Yb, np.expm1(np.minimum(Yb, 0.0)))
+    tol = tol_for("f32")
+    for by in (0, 1):
+        xs, gs = _shifted(xd, by), _shifted(gd, by)
+        for plan, plan_t in zip(_plans(cg, rp, cl, g, W, H), _plans(cg, cp_d, rt_d, gt, W, H)):
+            Y, buf = _guarded((g.n_rows, H, D), torch.float32, by)
+            Y2, buf2 = _guarded((g.n_rows, H, D), torch.float32, by)
+            al, abuf = _guarded((g.nnz, H), torch.float32, 0)
+            cg.gat_aggregate(rp, cl, sd_d, ss_d, xs, 0.2, plan=plan, out=Y)
+            cg.gat_aggregate(rp, cl, sd_d, ss_d, xs, 0.2, plan=plan, out=Y2, alpha_out=al)
+            assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= tol, (H, D, by)
+            assert torch.equal(Y, Y2) and _alpha_ok(al, g, sd, ss), (H, D, by)
+            for b in (buf, buf2):
+                _untouched(b, g.n_rows * W, by)
+            _untouched(abuf, g.nnz * H, 0)
+            Yg = cg.gat_aggregate(rp, cl, None, None, xs, 0.2, alpha_in=al_d, plan=plan, out_dtype=torch.float32)
+            assert scaled_error(Yg.reshape(Yr.shape), Yr, Ar) <= tol, (H, D, by, "given weights")
+            Ye = cg.gat_aggregate(rp, cl, sd_d, ss_d, xs, 0.2, plan=plan, out_dtype=torch.float32, bias=dev(bias),
+                                  act="elu")
+            assert scaled_error(Ye.reshape(Yr.shape), Yb, Ar + np.abs(bias)) <= tol, (H, D, by, "elu")
+            Ys, st = cg.gat_aggregate_stats(rp, cl, sd_d, xs, s_src=ss_d, negative_slope=0.2, plan=plan,
+                                            out_dtype=torch.float32)
+            assert torch.equal(Y, Ys), (H, D, by, "stats")
+            args = (rp, cl, cp_d, rt_d, pm_d, sd_d, ss_d)
+            a = cg.gat_backward(*args, al, xs, gs, 0.2, plan=plan, plan_t=plan_t, dx_dtype=torch.float32)
+            b = cg.gat_backward(*args, None, xs, gs, 0.2, plan=plan, plan_t=plan_t, dx_dtype=torch.float32,
+                                row_stats=st)
+            for k in a:
+                assert torch.equal(a[k], b[k]), (H, D, by, k)
+
+
+@pytest.mark.parametrize("H,D,xk", [(4, 32, "bf16"), (8, 16, "f32"), (1, 8, "f16"), (3, 16, "bf16"), (2, 128, "bf16"),
+                                    (5, 4, "f32"), (1, 512, "bf16"), (8, 64, "f16"), (2, 8, "f32")])
+def test_head_maps_projected(cg, H, D, xk):
+    """Projected source scores over every number of lanes that share a batch's scores, against
+    the aggregation on the scores in fp64 (bound: the aggregation's, plus each score's rounding
+    2 (D 2^-24 max sum|x a| + 2^-24 max|s|))."""
+    import torch
+    g = _graph(H * D + 2)
+    W = H * D
+    say(f"projected H={H} D={D} {xk}")
+    rp, cl, _ = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, H, D), 900 + W, xk)
+    rng = np.random.default_rng(W)
+    a = (rng.standard_normal((H, D)) / np.sqrt(D)).astype(np.float32)
+    sd = rng.standard_normal((g.n_rows, H)).astype(np.float32)
+    x64 = oracle.decode(xh, xc).reshape(g.n_cols, H, D)
+    s64 = (x64 * a.astype(np.float64)).sum(-1)
+    ss = s64.astype(np.float32)
+    Yr, Ar = oracle.gat(g.rowptr, g.col, sd, ss, xh.reshape(g.n_cols, W), H, D, slope=0.2, x_dtype=xc)
+    extra = 2 * (D * 2.0 ** -24 * (np.abs(x64) * np.abs(a)).sum(-1).max() + 2.0 ** -24 * np.abs(s64).max())
+    for plan in _plans(cg, rp, cl, g, W, H):
+        Y, buf = _guarded((g.n_rows, H, D), torch.float32, 0)
+        cg.gat_aggregate_proj(rp, cl, dev(sd), dev(a), xd, 0.2, plan=plan, out=Y)
+        assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= TOL_F32 + extra, (H, D)
+        _untouched(buf, g.n_rows * W, 0)
