@@ -26,14 +26,18 @@ template <> struct Fmt<f16_t> { static constexpr int bytes = 2; static constexpr
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// fp32 -> bf16, round to nearest even; NaN stays a quiet NaN.
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
+// Two fp32 -> two packed bf16 (lo in the low half), round to nearest even, NaN stays a
+// quiet NaN: one v_cvt_pk_bf16_f32, whose result equals the integer rounding
+// (u + 0x7fff + bit 16) >> 16, NaN | 0x40, for every fp32 pattern.
+__device__ __forceinline__ uint32_t f32x2_to_bf16(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
+    typedef __bf16 bf16x2_cvt __attribute__((ext_vector_type(2)));
+    typedef float f32x2_cvt __attribute__((ext_vector_type(2)));
+    const f32x2_cvt v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_cvt));
 }
+
+__device__ __forceinline__ uint32_t f32_to_bf16(float f) { return f32x2_to_bf16(f, f) & 0xffffu; }
 
 __device__ __forceinline__ float f16_bits_to_f32(uint32_t h)
 {
@@ -128,18 +132,18 @@ template <>
 __device__ __forceinline__ void store_vec<bf16_t, 8>(bf16_t *__restrict__ p, int64_t i, const float (&v)[8])
 {
     u32x4_u w;
-    w.x = f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16);
-    w.y = f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16);
-    w.z = f32_to_bf16(v[4]) | (f32_to_bf16(v[5]) << 16);
-    w.w = f32_to_bf16(v[6]) | (f32_to_bf16(v[7]) << 16);
+    w.x = f32x2_to_bf16(v[0], v[1]);
+    w.y = f32x2_to_bf16(v[2], v[3]);
+    w.z = f32x2_to_bf16(v[4], v[5]);
+    w.w = f32x2_to_bf16(v[6], v[7]);
     *reinterpret_cast<u32x4_u *>(p + i) = w;
 }
 template <>
 __device__ __forceinline__ void store_vec<bf16_t, 4>(bf16_t *__restrict__ p, int64_t i, const float (&v)[4])
 {
     u32x2_u w;
-    w.x = f32_to_bf16(v[0]) | (f32_to_bf16(v[1]) << 16);
-    w.y = f32_to_bf16(v[2]) | (f32_to_bf16(v[3]) << 16);
+    w.x = f32x2_to_bf16(v[0], v[1]);
+    w.y = f32x2_to_bf16(v[2], v[3]);
     *reinterpret_cast<u32x2_u *>(p + i) = w;
 }
 template <>

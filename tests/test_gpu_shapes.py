@@ -239,3 +239,36 @@ def test_head_maps_projected(cg, H, D, xk):
         cg.gat_aggregate_proj(rp, cl, dev(sd), dev(a), xd, 0.2, plan=plan, out=Y)
         assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= TOL_F32 + extra, (H, D)
         _untouched(buf, g.n_rows * W, 0)
+
+
+@pytest.mark.parametrize("F,G", [(64, 64), (100, 64), (1, 64), (63, 128), (65, 64), (129, 128), (256, 256), (300, 256),
+                                 (512, 512), (515, 512), (192, 192), (320, 64), (1030, 512), (1024, 1024), (700, 1024)])
+@pytest.mark.parametrize("xk", ["f32", "bf16", "f16"])
+def test_codec_widths_and_alignment(cg, F, G, xk):
+    """Every code width on whole, ragged, unaligned and odd-sized groups: codes, minima, steps and
+    decoded values bit for bit, nothing written past them."""
+    import torch
+    n = 37
+    say(f"codec F={F} G={G} {xk}")
+    xh, xc, xd = features((n, F), 50 + F, xk)
+    for by in (0, 1):
+        xs = _shifted(xd, by)
+        for bits in range(1, 9):
+            seed = 0x123456789ABC + bits + F
+            words, nst = cg.act_codec_size(n, F, bits, G)
+            codes, cbuf = _guarded((words,), torch.int64, 0)
+            stats, sbuf = _guarded((nst,), torch.float32, 0)
+            cg.act_compress(xs, bits, G, seed, codes=codes, stats=stats)
+            c_ref, s_ref = oracle.act_compress(xh, bits, G, seed, a_dtype=xc)
+            assert np.array_equal(codes.cpu().numpy().view(np.uint64), c_ref), (F, G, bits, by)
+            assert np.array_equal(stats.cpu().numpy().view(np.uint32), s_ref.view(np.uint32)), (F, G, bits, by)
+            out, obuf = _guarded((n, F), torch.float32, by)
+            cg.act_decompress(codes, stats, n, F, bits, G, out=out)
+            y_ref = oracle.act_decompress(c_ref, s_ref, n, F, bits, G)
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), y_ref.view(np.uint32)), (F, G, bits, by)
+            o16, o16buf = _guarded((n, F), torch.bfloat16, by)
+            cg.act_decompress(codes, stats, n, F, bits, G, out=o16)
+            assert np.array_equal(o16.cpu().view(torch.int16).numpy().view(np.uint16),
+                                  oracle.round_to(y_ref.astype(np.float64), oracle.BF16)), (F, G, bits, by)
+            for b, m, k in ((cbuf, words, 0), (sbuf, nst, 0), (obuf, n * F, by), (o16buf, n * F, by)):
+                _untouched(b, m, k)
