@@ -192,6 +192,195 @@ __global__ __launch_bounds__(kBlock) void k_linear(LinearArgs a)
     }
 }
 
+// The streaming form for many rows: a persistent workgroup of 8 wavefronts keeps its
+// 32 * NT rows of W in LDS for its whole life and every wavefront walks 32-row tiles of X
+// on its own, so nothing waits at a barrier: X goes from memory to the MFMA operand
+// registers, kStreamDepth chunks of 64 k ahead, across tile boundaries.  W is the first
+// MFMA operand, so that a lane ends with 16 outputs of one row: exchanges between the
+// wavefront's halves turn them into 16-byte stores.  Rows are cut into slots of 8 k; the
+// last one, when ragged, moves back to the row's end with its overlap zeroed in both
+// operands, and W has one more slot of zeros for the steps past it.  The ny column
+// blocks of the same rows run side by side on one XCD, so X is fetched once.  Bound by
+// the reads of X (3.4 TB/s of X and Y on 233k x 602 -> 128, 2.6 with k_linear); four or
+// five chunks ahead were slower or no faster.
+constexpr int kStreamBlock = 512;
+constexpr int kStreamDepth = 3;
+constexpr int kStreamLds = 160 * 1024;
+constexpr int64_t kStreamMinRows = 2048;
+
+struct StreamArgs {
+    LinearArgs l;
+    int32_t ny;        // column blocks
+    int32_t slots;     // slots of 8 k per row
+    int32_t row16;     // 16-byte words of a row of W in LDS (odd: no bank conflicts)
+};
+
+// 16 raw bytes at any 2-byte alignment
+template <typename T>
+__device__ __forceinline__ uint4 load8_any(const T *p)
+{
+    const u32x4_u v = *reinterpret_cast<const u32x4_u *>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// The last 8 - over of 8 packed elements, the first `over` zeroed.
+__device__ __forceinline__ uint4 drop_front(uint4 v, int over)
+{
+    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        w[i] &= (2 * i >= over ? 0x0000ffffu : 0u) | (2 * i + 1 >= over ? 0xffff0000u : 0u);
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Stores 8 consecutive outputs from column c on (those below m).
+template <typename TY>
+__device__ __forceinline__ void store8(TY *__restrict__ row, int c, int m, const float (&v)[8])
+{
+    if (c + 8 <= m) {
+        store_vec<TY, 8>(row, c, v);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float one[1] = {v[e]};
+            if (c + e < m) store_out<TY, 1>(row, c + e, one);
+        }
+    }
+}
+
+template <typename T, typename TY, int NT>
+__global__ __launch_bounds__(kStreamBlock, 2) void k_linear_stream(StreamArgs a)
+{
+    extern __shared__ uint4 sW[];                // [32 NT][row16], then the bias
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+    const int i = lane & 31, kq = lane >> 5;
+    const int ny = a.ny, row16 = a.row16, slots = a.slots, k = a.l.k, m = a.l.m;
+    const int y = ((int)blockIdx.x >> 3) % ny;
+    const int x = ((int)blockIdx.x & 7) + 8 * (((int)blockIdx.x >> 3) / ny);
+    const int gx = (int)gridDim.x / ny;
+    const int c0 = y * 32 * NT;
+    const T *__restrict__ X = static_cast<const T *>(a.l.X);
+    const T *__restrict__ W = static_cast<const T *>(a.l.W);
+    float *const sBias = reinterpret_cast<float *>(sW + 32 * NT * row16);
+    const int64_t tiles = (a.l.n + 31) / 32;
+    const int64_t step = (int64_t)gx * (kStreamBlock / kWave);
+    int64_t tile = (int64_t)x * (kStreamBlock / kWave) + wave;      // tile being summed
+    const int nch = (k + 63) / 64;
+    const int full = k / 64;             // chunks without a tail
+    // the loads' position: kStreamDepth chunks ahead
+    int64_t ltile = tile;
+    int lc = 0;
+    const auto row_of = [&](int64_t t) {
+        const int64_t r = t * 32 + i;
+        return X + (r < a.l.n ? r : a.l.n - 1) * k;
+    };
+    const T *lrow = row_of(ltile < tiles ? ltile : 0);
+    const auto issue = [&](uint4 (&q)[4]) {
+        if (ltile >= tiles) return;
+        const T *p = lrow + lc * 64 + kq * 8;
+        if (lc < full) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) q[s] = load8_any(p + 16 * s);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int slot = lc * 8 + 2 * s + kq;
+                const int over = 8 * slot + 8 > k ? 8 * slot + 8 - k : 0;
+                q[s] = make_uint4(0u, 0u, 0u, 0u);
+                if (slot < slots) q[s] = load8_any(p + 16 * s - over);
+            }
+        }
+        if (++lc == nch) {
+            lc = 0;
+            ltile += step;
+            if (ltile < tiles) lrow = row_of(ltile);
+        }
+    };
+    uint4 q[kStreamDepth][4];
+#pragma unroll
+    for (int u = 0; u < kStreamDepth; ++u) issue(q[u]);
+    // W, while the first chunks of X are on their way
+    // (batches of loads in flight: one at a time took 20 us of every call)
+    constexpr int kBatch = 10;
+    const int words = 32 * NT * row16;
+    for (int w0 = tid; w0 < words; w0 += kBatch * kStreamBlock) {
+        uint4 v[kBatch];
+        int over[kBatch];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            const int w = w0 + b * kStreamBlock;
+            const int r = w / row16, s = w - r * row16;
+            const bool in = w < words && c0 + r < m && s < slots;
+            over[b] = in ? (8 * s + 8 > k ? 8 * s + 8 - k : 0) : 8;
+            v[b] = load8_any(W + (in ? (int64_t)(c0 + r) * k + 8 * s - over[b] : 0));
+        }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b)
+            if (w0 + b * kStreamBlock < words) sW[w0 + b * kStreamBlock] = drop_front(v[b], over[b]);
+    }
+    for (int c = tid; c < 32 * NT; c += kStreamBlock) sBias[c] = (a.l.bias && c0 + c < m) ? a.l.bias[c0 + c] : 0.f;
+    __syncthreads();
+    if (tile >= tiles) return;
+    f32x16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    int c = 0;
+    TY *__restrict__ Y = static_cast<TY *>(a.l.Y);
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < kStreamDepth; ++u) {
+            const uint4 *wp = sW + i * row16;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                int slot = c * 8 + 2 * s + kq;
+                uint4 xf = q[u][s];
+                if (c >= full) {                                   // (uniform) the chunk with the tail
+                    if (c * 8 + 2 * s >= slots) break;                 // both halves past the row
+                    const int over = 8 * slot + 8 > k ? 8 * slot + 8 - k : 0;
+                    xf = drop_front(xf, over < 8 ? over : 8);
+                    slot = slot < slots ? slot : slots;
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    acc[t] = mfma_32x32x16<T>(wp[32 * t * row16 + slot], xf, acc[t]);
+            }
+            issue(q[u]);
+            if (++c < nch) continue;
+            // register r of lane l: output column 8 (r / 4) + 4 (l / 32) + r % 4 of row l % 32
+            c = 0;
+            const int64_t row = tile * 32 + i;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int g = 0; g < 4; g += 2) {
+                    // groups g and g + 1 of 8 columns: lower lanes keep g's 4 and take its other 4
+                    // from the upper lanes, which keep and take those of g + 1
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[t][4 * g + e]),
+                                                                         __float_as_uint(acc[t][4 * g + 4 + e]),
+                                                                         false, false);
+                        v[e] = __uint_as_float(sw[0]);
+                        v[4 + e] = __uint_as_float(sw[1]);
+                    }
+                    const int col = 32 * t + 8 * (g + kq);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = apply_act(v[e] + sBias[col + e], a.l.act);
+                    if (row < a.l.n && c0 + col < m) store8<TY>(Y + row * m, c0 + col, m, v);
+                }
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+            tile += step;
+            if (tile >= tiles) return;
+        }
+    }
+}
+
 // s_src[i, h] = sum_d Z[i, h, d] a_src[h, d] and s_dst likewise; a wavefront
 // per node (grid-stride), lanes over d.
 template <typename T>
@@ -289,6 +478,24 @@ unsigned score_blocks(int64_t n, int64_t per_block, const void *kernel)
     return (unsigned)blocks;
 }
 
+using StreamKernel = void (*)(StreamArgs);
+
+template <typename T, typename TY>
+StreamKernel pick_stream_nt(int nt)
+{
+    if (nt == 1) return k_linear_stream<T, TY, 1>;
+    if (nt == 2) return k_linear_stream<T, TY, 2>;
+    return k_linear_stream<T, TY, 4>;
+}
+
+template <typename T>
+StreamKernel pick_stream(int ydt, int nt)
+{
+    if (ydt == COGDL_F32) return pick_stream_nt<T, float>(nt);
+    if (ydt == COGDL_BF16) return pick_stream_nt<T, bf16_t>(nt);
+    return pick_stream_nt<T, f16_t>(nt);
+}
+
 using LinearKernel = void (*)(LinearArgs);
 
 // NT: 32-column tiles per workgroup, the fewest that cover m up to 128.
@@ -338,6 +545,27 @@ cogdl_status cogdl_linear(int64_t n, int32_t k, int32_t m, const void *X, const 
     const int64_t row_blocks = (n + kRowsPerBlock - 1) / kRowsPerBlock;
     if (row_blocks > INT32_MAX) return COGDL_ERR_TOO_LARGE;
     LinearArgs a{n, k, m, X, W, bias, (int32_t)act, Y};
+    const int nt = m <= 32 ? 1 : m <= 64 ? 2 : 4;
+    const int slots = (k + 7) / 8, row16 = (slots + 1) | 1;
+    const size_t lds = (size_t)32 * nt * row16 * 16 + 32 * nt * sizeof(float);
+    const int ny = (m + 32 * nt - 1) / (32 * nt);
+    // The streaming kernel from 2048 rows on where W fits in LDS: 602 -> 128 bf16 on 2.7k /
+    // 233k rows 30 -> 22 and 133 -> 101 us, 128 -> 48 31 -> 23, 135 -> 256 (odd rows) 189 -> 72.
+    // Short rows with wide outputs (24 -> 300: 100 against 113 us) stay with k_linear, whose
+    // stores cover 64 bytes of a row instead of 32.
+    if (k >= 8 && lds <= kStreamLds && n >= kStreamMinRows && (k >= 48 || m <= 128)) {
+        StreamArgs s{a, ny, slots, row16};
+        StreamKernel kern = dtype == COGDL_BF16 ? pick_stream<bf16_t>((int)y_dtype, nt)
+                                                : pick_stream<f16_t>((int)y_dtype, nt);
+        // resident workgroups (as many as their LDS allows), a multiple of 8 for each column block
+        const int64_t res = resident_blocks(reinterpret_cast<const void *>(kern), kStreamBlock, lds);
+        if (res < 1) return COGDL_ERR_LAUNCH;
+        int64_t gx = ((n + 31) / 32 + kStreamBlock / kWave - 1) / (kStreamBlock / kWave);
+        if (gx > res / ny) gx = res / ny;
+        gx = (gx + 7) / 8 * 8;
+        COGDL_LAUNCH_SHM("linear", kern, dim3((unsigned)(gx * ny)), kStreamBlock, lds, stream, s);
+        return COGDL_OK;
+    }
     const int mode = (k % 8 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0) ? 0
                      : (k % 2 == 0 && (uintptr_t)X % 4 == 0 && (uintptr_t)W % 4 == 0) ? 1 : 2;
     LinearKernel kern = dtype == COGDL_BF16 ? pick_linear_y<bf16_t>((int)y_dtype, mode, m)

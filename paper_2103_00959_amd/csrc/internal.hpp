@@ -129,9 +129,9 @@ inline int64_t list_grid(int64_t blocks, int lists)
 
 const Plan *plan_of(const cogdl_plan *h);
 
-// Workgroups of `block` threads of `kernel` that fit on the device at once
-// (all compute units), cached per kernel.
-int resident_blocks(const void *kernel, int block);
+// Workgroups of `block` threads of `kernel` with `shm` bytes of dynamic LDS that fit on
+// the device at once (all compute units), cached per kernel and shm.
+int resident_blocks(const void *kernel, int block, size_t shm = 0);
 
 // Y[row] = sum of the partial rows of every split row of the plan (F columns),
 // divided by the row's degree when `mean`, then act(. + bias) when given.

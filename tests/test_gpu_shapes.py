@@ -272,3 +272,27 @@ def test_codec_widths_and_alignment(cg, F, G, xk):
                                   oracle.round_to(y_ref.astype(np.float64), oracle.BF16)), (F, G, bits, by)
             for b, m, k in ((cbuf, words, 0), (sbuf, nst, 0), (obuf, n * F, by), (o16buf, n * F, by)):
                 _untouched(b, m, k)
+
+
+@pytest.mark.parametrize("k,m", [(8, 1), (9, 7), (15, 41), (16, 32), (17, 33), (47, 129), (48, 129), (63, 64), (64, 65), (65, 128),
+                                 (129, 300), (602, 128), (623, 127), (624, 97), (640, 97), (1160, 32), (1433, 16)])
+@pytest.mark.parametrize("n", [2047, 2048, 2081])
+@pytest.mark.parametrize("xk,yk", [("bf16", "f32"), ("f16", "f16")])
+def test_linear_streamed_shapes(cg, k, m, n, xk, yk):
+    """The dense layer around the streaming kernel's limits: slots and chunks of k, column tiles,
+    ragged row tiles, unaligned operands and outputs."""
+    import torch
+    say(f"linear n={n} k={k} m={m} {xk}->{yk}")
+    xh, xc, xd = features((n, k), 7 + k, xk)
+    wh, wc, wd = features((m, k), 8 + m, xk)
+    bias = np.random.default_rng(m).standard_normal(m).astype(np.float32)
+    ydt = torch.float32 if yk == "f32" else torch.float16
+    x64, w64 = oracle.decode(xh, xc).reshape(n, k), oracle.decode(wh, wc).reshape(m, k)
+    Yr = np.maximum(x64 @ w64.T + bias, 0.0)
+    Ar = np.abs(x64) @ np.abs(w64).T + np.abs(bias)
+    for by in (0, 1):
+        out, buf = _guarded((n, m), ydt, by)
+        cg.linear(_shifted(xd, by), _shifted(wd, by), dev(bias), act="relu", out=out)
+        # fp32 accumulation of exact products: k 2^-24 of the terms' sum at most; fp16 also rounds the result
+        assert scaled_error(out, Yr, Ar) <= k * 2.0 ** -24 + (0 if yk == "f32" else 1e-6), (k, m, n, by)
+        _untouched(buf, n * m, by)
