@@ -376,6 +376,55 @@ __device__ __forceinline__ float group_sum(float v, int G)
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+__device__ __forceinline__ int wave_inclusive_scan(int x)
+{
+    const int lane = lane_id();
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        int y = __builtin_amdgcn_ds_bpermute((lane >= d ? lane - d : lane) << 2, x);
+        if (lane >= d) x += y;
+    }
+    return x;
+}
+
+// Exclusive scans of K values per thread across a block of WAVES wavefronts, side by side
+// (one pair of barriers for all of them): x[c] becomes the exclusive prefix, total[c]
+// the block's sum.
+template <int K, int WAVES = 4>
+__device__ __forceinline__ void block_exclusive_scans(int (&x)[K], int (&total)[K])
+{
+    __shared__ int wsum[K][WAVES];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    int inc[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        inc[c] = wave_inclusive_scan(x[c]);
+        if (lane == kWave - 1) wsum[c][w] = inc[c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        int before = 0, all = 0;
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) {
+            if (i < w) before += wsum[c][i];
+            all += wsum[c][i];
+        }
+        total[c] = all;
+        x[c] = before + inc[c] - x[c];
+    }
+    __syncthreads();
+}
+
+template <int WAVES = 4>
+__device__ __forceinline__ int block_exclusive_scan(int v, int *total)
+{
+    int x[1] = {v}, t[1];
+    block_exclusive_scans<1, WAVES>(x, t);
+    *total = t[0];
+    return x[0];
+}
+
 // Rows of CSR edges, resolved by one wavefront (all 64 lanes, uniform control
 // flow) for edges handed over in increasing order.  start(e0) finds the row
 // holding edge e0 by a 64-way search of rowptr (each round narrows the

@@ -38,20 +38,20 @@ struct Plan {
     int4 *units_tmp = nullptr;    // [cap_units] row order (build scratch)
     int4 *split_rows = nullptr;   // [cap_split] {row, first partial slot, #slots, degree}
     int4 *part_units = nullptr;   // [cap_partials] {row, beg, end, split index}
-    int32_t *row_units = nullptr; // [n_rows + 1] exclusive scan; [n_rows] = #units
-    int32_t *row_parts = nullptr; // [n_rows + 1]; [n_rows] = #partial slots
-    int32_t *row_split = nullptr; // [n_rows + 1]; [n_rows] = #split rows
+    int32_t *row_units = nullptr; // [n_rows + 1] units of each row; [n_rows] = #units
+    int32_t *n_parts = nullptr;   // #partial slots
+    int32_t *n_split = nullptr;   // #split rows
+    uint32_t *block_sums = nullptr; // 8 sums of each workgroup of the count pass
     int32_t *counters = nullptr;  // [8]: 0 close-degree rows, 1 chosen mode,
                                   //      2 units longer than kTinyUnit, 3 zero,
                                   //      4 sliced plan: 1 when its rows were sliced,
                                   //      5 1 when the last build's totals exceeded the
                                   //        capacities (the plan was left empty)
+                                  //      6 which row counts the build used
     uint32_t *sort_keys = nullptr;   // [4 * cap_units]: keys, 2 ping buffers, sorted keys
     uint32_t *sort_vals = nullptr;   // [3 * cap_units]: order, then 2 ping buffers
     void *sort_ws = nullptr;
     size_t sort_ws_bytes = 0;
-    void *scan_ws = nullptr;
-    size_t scan_ws_bytes = 0;
     float *partials = nullptr;    // [cap_partials * max_feat]
     int32_t *parg = nullptr;      // [cap_partials * max_feat] edge ids of partial maxima
     float *gstats = nullptr;      // [cap_partials * max_heads * 2] per-group (m, z)
@@ -68,18 +68,16 @@ struct Plan {
     int32_t key_bits = 0;         // bits of the in-list sort key (group_size - size)
     void *base2 = nullptr;        // second allocation (sliced plans)
     int32_t *lists_tbl = nullptr; // [3 * kSlices]: list starts, ends of the long units, list ends
-    int32_t *alt_units = nullptr; // [n_rows + 1] x 3: the unsliced counts, used when the
-    int32_t *alt_parts = nullptr; //   sliced ones exceed the capacities
-    int32_t *alt_split = nullptr;
+    int32_t *alt_units = nullptr; // [n_rows + 1]: the unsliced counts, used when the sliced
+                                  //   ones exceed the capacities
     int32_t *row_cuts = nullptr;  // [n_rows][kSlices - 1]: the inner cuts of each sliced row
     unsigned long long *totals = nullptr;  // [3]: sliced units, partial slots, split rows
-    unsigned long long *block_totals = nullptr;  // [3 per workgroup of the count pass]
 
     const int32_t *n_units_dev() const { return row_units + n_rows; }
     const int32_t *n_big_dev() const { return counters + 2; }
     const int32_t *zero_dev() const { return counters + 3; }
-    const int32_t *n_split_dev() const { return row_split + n_rows; }
-    const int32_t *n_parts_dev() const { return row_parts + n_rows; }
+    const int32_t *n_split_dev() const { return n_split; }
+    const int32_t *n_parts_dev() const { return n_parts; }
 };
 
 // Units of at most this many edges run in the narrow-sub-group path.
@@ -143,14 +141,6 @@ int trace_begin(const char *name, hipStream_t s);
 void trace_end(int slot, hipStream_t s);
 
 // ---------------------------------------------------------- primitives
-
-// Exclusive prefix sum of n int32 values; out has n + 1 entries and out[n]
-// receives the total.  in and out may alias.  Workspace size from
-// scan_workspace_bytes(n, 1).  exclusive_scan3 scans three arrays of n + 1
-// entries in place with the launches of one (workspace scan_workspace_bytes(n, 3)).
-size_t scan_workspace_bytes(int64_t n, int arrays = 1);
-hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, void *ws, hipStream_t s);
-hipError_t exclusive_scan3(int32_t *a0, int32_t *a1, int32_t *a2, int64_t n, void *ws, hipStream_t s);
 
 // An extra 32-bit array carried through a radix sort: read from `in`,
 // written in sorted order to `out`; `ping` is 2 * n elements of scratch.

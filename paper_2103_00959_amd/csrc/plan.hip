@@ -30,123 +30,7 @@ struct cogdl_plan {
 namespace cogdl {
 namespace {
 
-// Rows whose degree is close to the average; one atomic per workgroup (a
-// grid-stride loop over a bounded grid keeps same-address atomics few).
-__global__ __launch_bounds__(256) void k_plan_close(const int32_t *__restrict__ rowptr, int32_t n_rows,
-                                                    int64_t nnz, int32_t *__restrict__ counters)
-{
-    __shared__ int wsum[4];
-    int close = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t d = (int64_t)rowptr[i + 1] - rowptr[i];
-        close += (2 * d * n_rows >= nnz && d * n_rows <= 2 * nnz) ? 1 : 0;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) close += __shfl_xor(close, off);
-    if (lane_id() == 0) wsum[threadIdx.x / kWave] = close;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int t = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        if (t) atomicAdd(&counters[0], t);
-    }
-}
-
-__device__ __forceinline__ int plan_mode(const int32_t *counters, int32_t n_rows, int req)
-{
-    if (req != COGDL_BALANCE_AUTO) return req;
-    return (10LL * counters[0] >= 9LL * n_rows) ? COGDL_BALANCE_ROW_SPLIT : COGDL_BALANCE_NEIGHBOR_GROUP;
-}
-
-__global__ void k_plan_counts(const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t G, int req,
-                              int32_t *__restrict__ counters, int32_t *__restrict__ row_units,
-                              int32_t *__restrict__ row_parts, int32_t *__restrict__ row_split)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int mode = plan_mode(counters, n_rows, req);
-    if (i == 0) counters[1] = mode;
-    if (i >= n_rows) return;
-    const int d = rowptr[i + 1] - rowptr[i];
-    int u = 1;
-    if (mode == COGDL_BALANCE_NEIGHBOR_GROUP && d > G) u = (d + G - 1) / G;
-    row_units[i] = u;
-    row_parts[i] = u > 1 ? u : 0;
-    row_split[i] = u > 1 ? 1 : 0;
-}
-
-// After the count scan: the totals (units, partial slots, split rows) of this
-// rowptr must fit the capacities the plan was allocated with.  They do
-// whenever rowptr[n_rows] is the nnz given at creation; a rowptr with more
-// edges would make the emit pass write past the plan's arrays, so instead the
-// totals are set to zero (an empty plan, no unit runs) and counters[5] = 1,
-// which cogdl_plan_query reports as COGDL_ERR_PLAN.
-__global__ void k_plan_check(int32_t *__restrict__ n_units, int32_t *__restrict__ n_parts,
-                             int32_t *__restrict__ n_split, int64_t cap_units, int64_t cap_partials,
-                             int64_t cap_split, int32_t *__restrict__ counters)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const bool fits = *n_units <= cap_units && *n_parts <= cap_partials && *n_split <= cap_split &&
-                      *n_units >= 0 && *n_parts >= 0 && *n_split >= 0;
-    if (!fits) {
-        *n_units = 0;
-        *n_parts = 0;
-        *n_split = 0;
-    }
-    counters[5] = fits ? 0 : 1;
-}
-
-// Emit the units of each row in row order, with their sort keys.
-__global__ void k_plan_emit(const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t G,
-                            const int32_t *__restrict__ counters,
-                            const int32_t *__restrict__ row_units,
-                            const int32_t *__restrict__ row_parts,
-                            const int32_t *__restrict__ row_split, int4 *__restrict__ units_tmp,
-                            uint32_t *__restrict__ keys, int4 *__restrict__ split_rows,
-                            int4 *__restrict__ part_units)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows || counters[5] != 0) return;
-    const bool ng = counters[1] == COGDL_BALANCE_NEIGHBOR_GROUP;
-    const int beg = rowptr[i], end = rowptr[i + 1];
-    const int u0 = row_units[i];
-    const int nu = row_units[i + 1] - u0;
-    if (nu == 1) {
-        units_tmp[u0] = make_int4(i, beg, end, -1);
-        const int size = end - beg;
-        keys[u0] = ng ? (uint32_t)(G - (size < G ? size : G)) : 0u;
-        return;
-    }
-    const int p0 = row_parts[i];
-    const int s = row_split[i];
-    split_rows[s] = make_int4(i, p0, nu, end - beg);
-    for (int g = 0; g < nu; ++g) {
-        const int b = beg + g * G;
-        const int e = (end - b > G) ? b + G : end;
-        units_tmp[u0 + g] = make_int4(i, b, e, p0 + g);
-        part_units[p0 + g] = make_int4(i, b, e, s);
-        keys[u0 + g] = (uint32_t)(G - (e - b));
-    }
-}
-
-// Units are sorted by key G - size (ascending): the tiny units (size <= T)
-// form the tail.  counters[2] = number of units longer than T (all of them
-// in row-split mode, whose keys are all 0), counters[3] = 0.
-__global__ void k_plan_split(const uint32_t *__restrict__ sorted_keys,
-                             const int32_t *__restrict__ n_units, int32_t G, int32_t T,
-                             int32_t *__restrict__ counters)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const uint32_t bound = G > T ? (uint32_t)(G - T) : 0u;
-    int32_t lo = 0, hi = *n_units;
-    while (lo < hi) {
-        const int32_t mid = lo + (hi - lo) / 2;
-        if (sorted_keys[mid] < bound) lo = mid + 1; else hi = mid;
-    }
-    counters[2] = (G > T) ? lo : *n_units;
-    counters[3] = 0;
-}
-
-// ----------------------------------------------------------- sliced plans
+constexpr int kPlanBlock = 256;
 
 // Cuts of row [beg, end) (end > beg) at the column-range boundaries: cut[s]
 // is the lower bound of column s * width in the row (a binary search over
@@ -183,185 +67,235 @@ __device__ __forceinline__ void slice_cuts(const int32_t *__restrict__ col, int 
     cut[kSlices] = end;
 }
 
-// The sliced unit count of row i (its cuts stored in row_cuts) after writing
-// its unsliced counts to the alt arrays.
-__device__ __forceinline__ int row_counts_sliced(const int32_t *__restrict__ rowptr,
-                                                      const int32_t *__restrict__ col, int i, int32_t G,
-                                                      int mode, int64_t width, int32_t slice_min,
-                                                      int32_t *__restrict__ alt_units,
-                                                      int32_t *__restrict__ alt_parts,
-                                                      int32_t *__restrict__ alt_split,
-                                                      int32_t *__restrict__ row_cuts)
-{
-    const int beg = rowptr[i], end = rowptr[i + 1];
-    const int d = end - beg;
-    const bool ng = mode == COGDL_BALANCE_NEIGHBOR_GROUP;
-    int u = (ng && d > G) ? ceil_div(d, G) : 1;
-    alt_units[i] = u;
-    alt_parts[i] = u > 1 ? u : 0;
-    alt_split[i] = u > 1 ? 1 : 0;
-    if (ng && d > slice_min) {
-        int cut[kSlices + 1];
-        slice_cuts(col, beg, end, width, cut);
-        u = 0;
-        for (int s = 0; s < kSlices; ++s) u += ceil_div(cut[s + 1] - cut[s], G);
-#pragma unroll
-        for (int s = 1; s < kSlices; ++s) row_cuts[(int64_t)i * (kSlices - 1) + s - 1] = cut[s];
-    }
-    return u;
-}
+// Sums of a workgroup's rows, 8 per workgroup: the rows whose degree is close to the
+// average, and the units, partial slots and split rows of the sliced (1-3; of a plain
+// plan: the only) and of the unsliced neighbour groups (4-6).  k_plan_totals puts the
+// sums over the workgroups before each one in 1-3.
+constexpr int kPlanSums = 8;
 
-// Per-row counts of a sliced plan: the sliced ones (a row with more than
-// slice_min edges gives ceil(len / G) units per nonempty slice), summed per
-// workgroup into block_totals, and, in the alt arrays, the
-// unsliced ones the build falls back to when the sliced totals exceed the
+// Per-row unit counts of the neighbour-group backend (the mode is not known yet), and
+// the pad keys of the sort.  A sliced row (more than slice_min edges) gives ceil(len /
+// G) units per nonempty slice, its cuts stored for k_plan_emit; alt_units keeps the
+// unsliced count, which the build falls back to when the sliced totals exceed the
 // plan's capacities.
-__global__ void k_plan_counts_sliced(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                                     int32_t n_rows, int32_t G, int req, int64_t width, int32_t slice_min,
-                                     int32_t *__restrict__ counters, int32_t *__restrict__ row_units,
-                                     int32_t *__restrict__ row_parts, int32_t *__restrict__ row_split,
-                                     int32_t *__restrict__ alt_units, int32_t *__restrict__ alt_parts,
-                                     int32_t *__restrict__ alt_split, int32_t *__restrict__ row_cuts,
-                                     unsigned long long *__restrict__ block_totals)
+template <bool SLICED>
+__global__ __launch_bounds__(kPlanBlock) void k_plan_counts(
+    const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int32_t n_rows, int64_t nnz, int32_t G,
+    int64_t width, int32_t slice_min, int32_t *__restrict__ row_units, int32_t *__restrict__ alt_units,
+    int32_t *__restrict__ row_cuts, uint32_t *__restrict__ sums, uint32_t *__restrict__ keys, int64_t n_keys,
+    uint32_t pad)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int mode = plan_mode(counters, n_rows, req);
-    if (i == 0) counters[1] = mode;
-    uint32_t su = 0, sp = 0, ss = 0;
+    for (int64_t k = (int64_t)blockIdx.x * kPlanBlock + threadIdx.x; k < n_keys; k += (int64_t)gridDim.x * kPlanBlock)
+        keys[k] = pad;
+    const int i = blockIdx.x * kPlanBlock + threadIdx.x;
+    uint32_t v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (i < n_rows) {
-        const int u = row_counts_sliced(rowptr, col, i, G, mode, width, slice_min, alt_units, alt_parts,
-                                        alt_split, row_cuts);
+        const int beg = rowptr[i], end = rowptr[i + 1];
+        const int d = end - beg;
+        v[0] = (2 * (int64_t)d * n_rows >= nnz && (int64_t)d * n_rows <= 2 * nnz) ? 1u : 0u;
+        const int alt = d > G ? ceil_div(d, G) : 1;
+        int u = alt;
+        if (SLICED && d > slice_min) {
+            int cut[kSlices + 1];
+            slice_cuts(col, beg, end, width, cut);
+            u = 0;
+            for (int s = 0; s < kSlices; ++s) u += ceil_div(cut[s + 1] - cut[s], G);
+#pragma unroll
+            for (int s = 1; s < kSlices; ++s) row_cuts[(int64_t)i * (kSlices - 1) + s - 1] = cut[s];
+        }
         row_units[i] = u;
-        row_parts[i] = u > 1 ? u : 0;
-        row_split[i] = u > 1 ? 1 : 0;
-        su = (uint32_t)u;
-        sp = u > 1 ? (uint32_t)u : 0u;
-        ss = u > 1 ? 1u : 0u;
+        if (SLICED) alt_units[i] = alt;
+        v[1] = (uint32_t)u;
+        v[2] = u > 1 ? (uint32_t)u : 0u;
+        v[3] = u > 1 ? 1u : 0u;
+        v[4] = (uint32_t)alt;
+        v[5] = alt > 1 ? (uint32_t)alt : 0u;
+        v[6] = alt > 1 ? 1u : 0u;
     }
-    // workgroup sums, one slot per workgroup (k_plan_fit adds them up: atomics
-    // from every wavefront on three addresses serialize)
-    __shared__ uint32_t wsum[3][256 / kWave];
-    const auto add = [](uint32_t a, uint32_t b) { return a + b; };
-    su = group_reduce(su, kWave, add);
-    sp = group_reduce(sp, kWave, add);
-    ss = group_reduce(ss, kWave, add);
-    const int w = threadIdx.x / kWave;
-    if (lane_id() == 0) {
-        wsum[0][w] = su;
-        wsum[1][w] = sp;
-        wsum[2][w] = ss;
+    __shared__ uint32_t wsum[7][kPlanBlock / kWave];
+#pragma unroll
+    for (int c = 0; c < 7; ++c) {
+        v[c] = group_reduce(v[c], kWave, [](uint32_t a, uint32_t b) { return a + b; });
+        if (lane_id() == 0) wsum[c][threadIdx.x / kWave] = v[c];
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
-        unsigned long long t = 0;
-        for (int j = 0; j < (int)(blockDim.x / kWave); ++j) t += wsum[threadIdx.x][j];
-        block_totals[(int64_t)blockIdx.x * 3 + threadIdx.x] = t;
+    if (threadIdx.x < 7) {
+        uint32_t s = 0;
+#pragma unroll
+        for (int w = 0; w < kPlanBlock / kWave; ++w) s += wsum[threadIdx.x][w];
+        sums[(int64_t)blockIdx.x * kPlanSums + threadIdx.x] = s;
     }
 }
 
-// counters[4] = 1 when the sliced totals fit the capacities (else the
-// unsliced counts replace them and no row is sliced).
-// The sliced totals (units, partial slots, split rows) from the workgroup sums
-// of k_plan_counts_sliced, in a fixed order (one workgroup of 256 threads).
-__global__ __launch_bounds__(256) void k_plan_fit(const unsigned long long *__restrict__ block_totals,
-                                                  int64_t n_blocks, int64_t cap_units, int64_t cap_partials,
-                                                  int64_t cap_split, unsigned long long *__restrict__ totals,
-                                                  int32_t *__restrict__ counters)
+// One workgroup: the totals, the mode (row split when at least 90% of the rows are close
+// to the average), which counts the build uses (counters[6]: 0 the sliced ones, 1 the
+// unsliced ones, 2 one unit per row), and each workgroup's first unit, partial slot and
+// split row, in a fixed order.  The totals must fit the capacities the plan was
+// allocated with.  They do whenever rowptr[n_rows] is the nnz given at creation; a
+// rowptr with more edges would make the emit pass write past the plan's arrays, so
+// instead the totals are set to zero (an empty plan, no unit runs) and counters[5] = 1,
+// which cogdl_plan_query reports as COGDL_ERR_PLAN.
+constexpr int kTotalsBlock = 1024;
+
+__global__ __launch_bounds__(kTotalsBlock) void k_plan_totals(uint32_t *__restrict__ sums, int64_t n_blocks,
+                                                              int32_t n_rows, int req, int sliced,
+                                                              int64_t cap_units, int64_t cap_partials,
+                                                              int64_t cap_split, unsigned long long *__restrict__ totals,
+                                                              int32_t *__restrict__ n_units,
+                                                              int32_t *__restrict__ n_parts,
+                                                              int32_t *__restrict__ n_split,
+                                                              int32_t *__restrict__ counters)
 {
-    __shared__ unsigned long long part[3][256];
-    unsigned long long t[3] = {0, 0, 0};
-    for (int64_t b = threadIdx.x; b < n_blocks; b += blockDim.x)
+    constexpr int kWaves = kTotalsBlock / kWave;
+    __shared__ unsigned long long part[7][kWaves];
+    __shared__ int set_sh;
+    unsigned long long t[7] = {0, 0, 0, 0, 0, 0, 0};
+    for (int64_t b = threadIdx.x; b < n_blocks; b += kTotalsBlock) {
+        const uint4 lo = *reinterpret_cast<const uint4 *>(sums + b * kPlanSums);
+        const uint4 hi = *reinterpret_cast<const uint4 *>(sums + b * kPlanSums + 4);
+        t[0] += lo.x; t[1] += lo.y; t[2] += lo.z; t[3] += lo.w;
+        t[4] += hi.x; t[5] += hi.y; t[6] += hi.z;
+    }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) t[c] += block_totals[b * 3 + c];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) part[c][threadIdx.x] = t[c];
+    for (int c = 0; c < 7; ++c) {
+        for (int off = kWave / 2; off > 0; off >>= 1) t[c] += __shfl_xor(t[c], off);
+        if (lane_id() == 0) part[c][threadIdx.x / kWave] = t[c];
+    }
     __syncthreads();
-    if (threadIdx.x < 3) {
+    if (threadIdx.x < 7) {
         unsigned long long sum = 0;
-        for (int j = 0; j < (int)blockDim.x; ++j) sum += part[threadIdx.x][j];
-        totals[threadIdx.x] = sum;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += part[threadIdx.x][w];
         part[threadIdx.x][0] = sum;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const bool fits = part[0][0] <= (unsigned long long)cap_units &&
-                          part[1][0] <= (unsigned long long)cap_partials &&
-                          part[2][0] <= (unsigned long long)cap_split;
-        counters[4] = fits ? 1 : 0;
+#pragma unroll
+        for (int c = 0; c < 7; ++c) t[c] = part[c][0];
+        const int mode = req != COGDL_BALANCE_AUTO ? req
+                         : 10ull * t[0] >= 9ull * (unsigned long long)n_rows ? (int)COGDL_BALANCE_ROW_SPLIT
+                                                                              : (int)COGDL_BALANCE_NEIGHBOR_GROUP;
+        const bool rows = mode == COGDL_BALANCE_ROW_SPLIT;
+        if (rows) {
+            t[1] = (unsigned long long)n_rows;
+            t[2] = t[3] = 0;
+        }
+        if (totals) {
+            totals[0] = t[1];
+            totals[1] = t[2];
+            totals[2] = t[3];
+        }
+        const auto fits = [&](int c) {
+            return t[c] <= (unsigned long long)cap_units && t[c + 1] <= (unsigned long long)cap_partials &&
+                   t[c + 2] <= (unsigned long long)cap_split;
+        };
+        int set = rows ? 2 : 0;
+        int c = 1;
+        if (!rows && sliced && !fits(1)) {
+            set = 1;
+            c = 4;
+        }
+        const bool ok = fits(c) && t[c] <= (unsigned long long)INT32_MAX && t[c + 1] <= (unsigned long long)INT32_MAX;
+        *n_units = ok ? (int32_t)t[c] : 0;
+        *n_parts = ok ? (int32_t)t[c + 1] : 0;
+        *n_split = ok ? (int32_t)t[c + 2] : 0;
+        counters[0] = (int32_t)t[0];
+        counters[1] = mode;
+        counters[2] = 0;
+        counters[3] = 0;
+        counters[4] = sliced && set != 1 ? 1 : 0;
+        counters[5] = ok ? 0 : 1;
+        counters[6] = set;
+        set_sh = ok ? set : -1;
+    }
+    __syncthreads();
+    const int set = set_sh;
+    if (set < 0) return;
+    int carry[3] = {0, 0, 0};
+    for (int64_t b0 = 0; b0 < n_blocks; b0 += kTotalsBlock) {
+        const int64_t b = b0 + threadIdx.x;
+        const bool in = b < n_blocks;
+        int x[3] = {0, 0, 0}, total[3];
+        if (in && set == 2) {
+            const int64_t left = n_rows - b * kPlanBlock;
+            x[0] = (int)(left < kPlanBlock ? left : kPlanBlock);
+        } else if (in) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) x[c] = (int)sums[b * kPlanSums + (set == 1 ? 4 : 1) + c];
+        }
+        block_exclusive_scans<3, kWaves>(x, total);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (in) sums[b * kPlanSums + 1 + c] = (uint32_t)(carry[c] + x[c]);
+            carry[c] += total[c];
+        }
     }
 }
 
-__global__ void k_plan_fallback(int32_t n_rows, const int32_t *__restrict__ counters,
-                                int32_t *__restrict__ row_units, int32_t *__restrict__ row_parts,
-                                int32_t *__restrict__ row_split, const int32_t *__restrict__ alt_units,
-                                const int32_t *__restrict__ alt_parts, const int32_t *__restrict__ alt_split)
+// The units of each row, in row order, with their sort keys: plain plans G - size
+// (neighbour groups; 0 for row split); sliced plans (list << kb) | that, slice s of a
+// sliced row in list s, every other unit in list row % kSlices.
+template <bool SLICED>
+__global__ __launch_bounds__(kPlanBlock) void k_plan_emit(
+    const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t G, int kb, int32_t slice_min,
+    const int32_t *__restrict__ row_cuts, const int32_t *__restrict__ counters, const uint32_t *__restrict__ sums,
+    const int32_t *__restrict__ row_units, const int32_t *__restrict__ alt_units, int4 *__restrict__ units_tmp,
+    uint32_t *__restrict__ keys, int4 *__restrict__ split_rows, int4 *__restrict__ part_units)
 {
-    if (counters[4] != 0) return;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        row_units[i] = alt_units[i];
-        row_parts[i] = alt_parts[i];
-        row_split[i] = alt_split[i];
-    }
-}
-
-// Units of a sliced plan with their sort keys (list << kb) | (G - size)
-// (neighbour groups; row split: list << kb).  Slice s of a sliced row is in
-// list s, every other unit in list row % kSlices.
-__global__ void k_plan_emit_sliced(const int32_t *__restrict__ rowptr, int32_t n_rows, int32_t G,
-                                   int kb, int32_t slice_min, const int32_t *__restrict__ row_cuts,
-                                   const int32_t *__restrict__ counters,
-                                   const int32_t *__restrict__ row_units,
-                                   const int32_t *__restrict__ row_parts,
-                                   const int32_t *__restrict__ row_split, int4 *__restrict__ units_tmp,
-                                   uint32_t *__restrict__ keys, int4 *__restrict__ split_rows,
-                                   int4 *__restrict__ part_units)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_rows || counters[5] != 0) return;
+    if (counters[5] != 0) return;
+    const int i = blockIdx.x * kPlanBlock + threadIdx.x;
+    const bool live = i < n_rows;
     const bool ng = counters[1] == COGDL_BALANCE_NEIGHBOR_GROUP;
-    const bool slice = ng && counters[4] != 0;
+    const int set = counters[6];
+    const int nu = !live ? 0 : set == 2 ? 1 : (SLICED && set == 1) ? alt_units[i] : row_units[i];
+    const uint32_t *first = sums + (int64_t)blockIdx.x * kPlanSums + 1;
+    int at[3] = {nu, nu > 1 ? nu : 0, nu > 1 ? 1 : 0}, all[3];
+    block_exclusive_scans<3>(at, all);
+    if (!live) return;
+    const int u0 = (int)first[0] + at[0], p0 = (int)first[1] + at[1], sidx = (int)first[2] + at[2];
     const int beg = rowptr[i], end = rowptr[i + 1];
     const int d = end - beg;
-    const int u0 = row_units[i];
-    const int nu = row_units[i + 1] - u0;
-    int cut[kSlices + 1];
-    const bool sliced_row = slice && d > slice_min;
-    if (sliced_row) {
-        // the cuts the count pass found (the same for the same columns)
-        cut[0] = beg;
+    const bool sliced_row = SLICED && set == 0 && d > slice_min;
+    const uint32_t home = SLICED ? (uint32_t)(i % kSlices) << kb : 0u;
+    int cut[SLICED ? kSlices + 1 : 1];
+    if constexpr (SLICED) {
+        if (sliced_row) {
+            // the cuts the count pass found (the same for the same columns)
+            cut[0] = beg;
 #pragma unroll
-        for (int s = 1; s < kSlices; ++s) cut[s] = row_cuts[(int64_t)i * (kSlices - 1) + s - 1];
-        cut[kSlices] = end;
+            for (int s = 1; s < kSlices; ++s) cut[s] = row_cuts[(int64_t)i * (kSlices - 1) + s - 1];
+            cut[kSlices] = end;
+        }
     }
     if (nu == 1) {
-        uint32_t list = (uint32_t)(i % kSlices);
-        if (sliced_row)
-            for (int s = 0; s < kSlices; ++s)
-                if (cut[s + 1] > cut[s]) list = (uint32_t)s;
-        units_tmp[u0] = make_int4(i, beg, end, -1);
-        keys[u0] = (list << kb) | (ng ? (uint32_t)(G - (d < G ? d : G)) : 0u);
-        return;
-    }
-    const int p0 = row_parts[i];
-    const int sidx = row_split[i];
-    split_rows[sidx] = make_int4(i, p0, nu, d);
-    if (sliced_row) {
-        int g = 0;
-        for (int s = 0; s < kSlices; ++s) {
-            for (int b = cut[s]; b < cut[s + 1]; b += G) {
-                const int e = (cut[s + 1] - b > G) ? b + G : cut[s + 1];
-                if (g < nu) {
-                    units_tmp[u0 + g] = make_int4(i, b, e, p0 + g);
-                    part_units[p0 + g] = make_int4(i, b, e, sidx);
-                    keys[u0 + g] = ((uint32_t)s << kb) | (uint32_t)(G - (e - b));
-                }
-                ++g;
-            }
+        uint32_t list = home;
+        if constexpr (SLICED) {
+            if (sliced_row)
+                for (int s = 0; s < kSlices; ++s)
+                    if (cut[s + 1] > cut[s]) list = (uint32_t)s << kb;
         }
+        units_tmp[u0] = make_int4(i, beg, end, -1);
+        keys[u0] = list | (ng ? (uint32_t)(G - (d < G ? d : G)) : 0u);
         return;
     }
-    const uint32_t home = (uint32_t)(i % kSlices) << kb;
+    split_rows[sidx] = make_int4(i, p0, nu, d);
+    if constexpr (SLICED) {
+        if (sliced_row) {
+            int g = 0;
+            for (int s = 0; s < kSlices; ++s) {
+                for (int b = cut[s]; b < cut[s + 1]; b += G) {
+                    const int e = (cut[s + 1] - b > G) ? b + G : cut[s + 1];
+                    if (g < nu) {
+                        units_tmp[u0 + g] = make_int4(i, b, e, p0 + g);
+                        part_units[p0 + g] = make_int4(i, b, e, sidx);
+                        keys[u0 + g] = ((uint32_t)s << kb) | (uint32_t)(G - (e - b));
+                    }
+                    ++g;
+                }
+            }
+            return;
+        }
+    }
     for (int g = 0; g < nu; ++g) {
         const int b = beg + g * G;
         const int e = (end - b > G) ? b + G : end;
@@ -371,52 +305,72 @@ __global__ void k_plan_emit_sliced(const int32_t *__restrict__ rowptr, int32_t n
     }
 }
 
-// The list table of a sliced plan from the sorted keys: for list x its first
-// unit, the end of its long units (keys below (x << kb) | (G - T)) and its
-// end; counters[2] = the long units of all lists, counters[3] = 0.
-__global__ void k_plan_lists(const uint32_t *__restrict__ sorted, const int32_t *__restrict__ n_units,
-                             int32_t G, int32_t T, int kb, int32_t *__restrict__ tbl,
-                             int32_t *__restrict__ counters)
+// First index of sorted[0, n) not below key, by a 64-way search of one wavefront.
+__device__ __forceinline__ int32_t wave_lower_bound(const uint32_t *__restrict__ sorted, int32_t n, uint32_t key)
 {
-    __shared__ int32_t longs[kSlices];
-    const int x = threadIdx.x;
-    if (x < kSlices) {
-        const int32_t n = *n_units;
-        const auto lb = [&](uint32_t key) {
-            int32_t lo = 0, hi = n;
-            while (lo < hi) {
-                const int32_t mid = lo + (hi - lo) / 2;
-                if (sorted[mid] < key) lo = mid + 1;
-                else hi = mid;
-            }
-            return lo;
-        };
-        const uint32_t base = (uint32_t)x << kb;
-        const int32_t lo = lb(base);
-        const int32_t hi = x + 1 < kSlices ? lb((uint32_t)(x + 1) << kb) : n;
-        const int32_t big = G > T ? lb(base | (uint32_t)(G - T)) : hi;
-        tbl[x] = lo;
-        tbl[kSlices + x] = big;
-        tbl[2 * kSlices + x] = hi;
-        longs[x] = big - lo;
+    int32_t lo = 0, hi = n;              // the answer is in [lo, hi]
+    while (lo < hi) {
+        const int32_t step = (hi - lo + kWave - 1) / kWave;
+        const int64_t p = (int64_t)lo + (int64_t)lane_id() * step;
+        // the probes below the key are a prefix of the lanes
+        const int below = __popcll(__ballot(p < hi && sorted[p] < key));
+        if (below == 0) return lo;
+        const int64_t last = (int64_t)lo + (int64_t)(below - 1) * step;
+        lo = (int32_t)last + 1;
+        hi = (int32_t)(last + step < hi ? last + step : hi);
     }
-    __syncthreads();
-    if (x == 0) {
-        int32_t t = 0;
-        for (int i = 0; i < kSlices; ++i) t += longs[i];
-        counters[2] = t;
-        counters[3] = 0;
-    }
+    return lo;
 }
 
-__global__ void k_plan_gather(const int4 *__restrict__ units_tmp, const uint32_t *__restrict__ order,
-                              const int32_t *__restrict__ n_units, int64_t cap,
-                              int4 *__restrict__ units)
+// The units in sorted order, and (workgroup 0) where the sorted units split.  They are
+// sorted by G - size (ascending), so the tiny ones (size <= T) form the tail of each
+// list.  Plain plans: counters[2] = number of units longer than T (all of them in
+// row-split mode, whose keys are all 0).  Sliced plans: for list x its first unit, the
+// end of its long units (keys below (x << kb) | (G - T)) and its end; counters[2] =
+// the long units of all lists.
+constexpr int kFinishBlock = 1024;
+
+__global__ __launch_bounds__(kFinishBlock) void k_plan_finish(const int4 *__restrict__ units_tmp,
+                                                              const uint32_t *__restrict__ order,
+                                                              const uint32_t *__restrict__ sorted,
+                                                              const int32_t *__restrict__ n_units, int64_t cap,
+                                                              int32_t G, int32_t T, int sliced, int kb,
+                                                              int32_t *__restrict__ tbl,
+                                                              int32_t *__restrict__ counters,
+                                                              int4 *__restrict__ units)
 {
-    const int64_t n = *n_units;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n && i < cap;
-         i += (int64_t)gridDim.x * blockDim.x)
+    const int32_t n = *n_units;
+    for (int64_t i = (int64_t)blockIdx.x * kFinishBlock + threadIdx.x; i < n && i < cap;
+         i += (int64_t)gridDim.x * kFinishBlock)
         units[i] = units_tmp[order[i]];
+    if (blockIdx.x != 0) return;
+    __shared__ int32_t bound[2 * kSlices];
+    const uint32_t big = G > T ? (uint32_t)(G - T) : 0u;
+    const int w = threadIdx.x / kWave;
+    if (!sliced) {
+        if (w == 0) {
+            const int32_t b = G > T ? wave_lower_bound(sorted, n, big) : n;
+            if (lane_id() == 0) counters[2] = b;
+        }
+        return;
+    }
+    static_assert(kFinishBlock / kWave == 2 * kSlices, "a wavefront per bound");
+    const uint32_t base = (uint32_t)(w / 2) << kb;
+    const int32_t b = wave_lower_bound(sorted, n, w % 2 ? base | big : base);
+    if (lane_id() == 0) bound[w] = b;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t longs = 0;
+        for (int x = 0; x < kSlices; ++x) {
+            const int32_t lo = bound[2 * x], hi = x + 1 < kSlices ? bound[2 * x + 2] : n;
+            const int32_t mid = G > T ? bound[2 * x + 1] : hi;
+            tbl[x] = lo;
+            tbl[kSlices + x] = mid;
+            tbl[2 * kSlices + x] = hi;
+            longs += mid - lo;
+        }
+        counters[2] = longs;
+    }
 }
 
 __global__ void k_plan_export(const int4 *__restrict__ units, const int32_t *__restrict__ n_units,
@@ -430,63 +384,60 @@ __global__ void k_plan_export(const int4 *__restrict__ units, const int32_t *__r
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Rows per unit-count pass; the sliced counts and their fallback.
-cogdl_status plan_counts_sliced(Plan &P, const int32_t *rowptr, const int32_t *col, hipStream_t s)
+// The row counts and totals of a rowptr (keys: the sort's keys to pad, or none).
+cogdl_status plan_count(Plan &P, const int32_t *rowptr, const int32_t *col, uint32_t *keys, int64_t n_keys,
+                        uint32_t pad, hipStream_t s)
 {
     const int n = P.n_rows;
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    const int64_t width = ((int64_t)P.n_cols + kSlices - 1) / kSlices;
-    COGDL_LAUNCH("plan_counts", k_plan_counts_sliced, blocks, 256, s, rowptr, col, n, P.group_size,
-                 (int)P.mode_req, width > 0 ? width : 1, P.slice_min, P.counters, P.row_units,
-                 P.row_parts, P.row_split, P.alt_units, P.alt_parts, P.alt_split, P.row_cuts,
-                 P.block_totals);
-    COGDL_LAUNCH("plan_fit", k_plan_fit, 1, 256, s, P.block_totals, (int64_t)blocks, P.cap_units,
-                 P.cap_partials, P.cap_split, P.totals, P.counters);
+    const unsigned blocks = (unsigned)((n + kPlanBlock - 1) / kPlanBlock);
+    if (P.sliced) {
+        const int64_t width = ((int64_t)P.n_cols + kSlices - 1) / kSlices;
+        // (a row-split plan asked for by the caller is never sliced)
+        const int32_t slice_min = P.mode_req == COGDL_BALANCE_ROW_SPLIT ? INT32_MAX : P.slice_min;
+        COGDL_LAUNCH("plan_counts", k_plan_counts<true>, blocks, kPlanBlock, s, rowptr, col, n, P.nnz,
+                     P.group_size, width > 0 ? width : 1, slice_min, P.row_units, P.alt_units, P.row_cuts,
+                     P.block_sums, keys, n_keys, pad);
+    } else {
+        COGDL_LAUNCH("plan_counts", k_plan_counts<false>, blocks, kPlanBlock, s, rowptr, nullptr, n, P.nnz,
+                     P.group_size, 1, 0, P.row_units, nullptr, nullptr, P.block_sums, keys, n_keys, pad);
+    }
+    COGDL_LAUNCH("plan_totals", k_plan_totals, 1, kTotalsBlock, s, P.block_sums, (int64_t)blocks, n,
+                 (int)P.mode_req, (int)P.sliced, P.cap_units, P.cap_partials, P.cap_split, P.totals,
+                 P.row_units + n, P.n_parts, P.n_split, P.counters);
     return COGDL_OK;
 }
 
+// Counts, totals, units in row order, the sort by length, the sorted units: five
+// launches beside the sort's three per pass (a build was 20 launches and is now 11 at
+// 12 key bits; column-sliced, 169k rows and 2.5M nonzeros 115 -> 74 us, 2.4M and 122M
+// 396 -> 330 us; plain 84 -> 63 and 194 -> 168 us).
 cogdl_status plan_build(Plan &P, const int32_t *rowptr, const int32_t *col, hipStream_t s)
 {
     const int n = P.n_rows;
-    COGDL_HIP_TRY(fill_i32(P.counters, 8, 0, s));
     const int32_t G = P.group_size;
     const int kb = P.sliced ? P.key_bits : 0;
     // Pad keys sort after every real unit; the sort covers the capacity.
     const uint32_t pad = P.sliced ? (((uint32_t)(kSlices - 1) << kb) | (uint32_t)(G + 1))
                                   : (uint32_t)G + 1u;
-    COGDL_HIP_TRY(fill_i32(reinterpret_cast<int32_t *>(P.sort_keys), P.cap_units, (int32_t)pad, s));
     if (n == 0) {
+        COGDL_HIP_TRY(fill_i32(P.counters, 8, 0, s));
         COGDL_HIP_TRY(fill_i32(P.row_units, 1, 0, s));
-        COGDL_HIP_TRY(fill_i32(P.row_parts, 1, 0, s));
-        COGDL_HIP_TRY(fill_i32(P.row_split, 1, 0, s));
+        COGDL_HIP_TRY(fill_i32(P.n_parts, 1, 0, s));
+        COGDL_HIP_TRY(fill_i32(P.n_split, 1, 0, s));
         if (P.sliced) COGDL_HIP_TRY(fill_i32(P.lists_tbl, 3 * kSlices, 0, s));
         return COGDL_OK;
     }
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    COGDL_LAUNCH("plan_close", k_plan_close, blocks < 512 ? blocks : 512, 256, s, rowptr, n, P.nnz,
-                 P.counters);
-    if (P.sliced) {
-        const cogdl_status st = plan_counts_sliced(P, rowptr, col, s);
-        if (st != COGDL_OK) return st;
-        COGDL_LAUNCH("plan_fallback", k_plan_fallback, blocks < 1024 ? blocks : 1024, 256, s, n,
-                     P.counters, P.row_units, P.row_parts, P.row_split, P.alt_units, P.alt_parts,
-                     P.alt_split);
-        COGDL_HIP_TRY(exclusive_scan3(P.row_units, P.row_parts, P.row_split, n, P.scan_ws, s));
-        COGDL_LAUNCH("plan_check", k_plan_check, 1, 64, s, P.row_units + n, P.row_parts + n,
-                     P.row_split + n, P.cap_units, P.cap_partials, P.cap_split, P.counters);
-        COGDL_LAUNCH("plan_emit", k_plan_emit_sliced, blocks, 256, s, rowptr, n, G, kb, P.slice_min,
-                     P.row_cuts, P.counters, P.row_units, P.row_parts, P.row_split, P.units_tmp,
-                     P.sort_keys, P.split_rows, P.part_units);
-    } else {
-        COGDL_LAUNCH("plan_counts", k_plan_counts, blocks, 256, s, rowptr, n, G, (int)P.mode_req,
-                     P.counters, P.row_units, P.row_parts, P.row_split);
-        COGDL_HIP_TRY(exclusive_scan3(P.row_units, P.row_parts, P.row_split, n, P.scan_ws, s));
-        COGDL_LAUNCH("plan_check", k_plan_check, 1, 64, s, P.row_units + n, P.row_parts + n,
-                     P.row_split + n, P.cap_units, P.cap_partials, P.cap_split, P.counters);
-        COGDL_LAUNCH("plan_emit", k_plan_emit, blocks, 256, s, rowptr, n, G, P.counters,
-                     P.row_units, P.row_parts, P.row_split, P.units_tmp, P.sort_keys, P.split_rows,
+    const unsigned blocks = (unsigned)((n + kPlanBlock - 1) / kPlanBlock);
+    const cogdl_status st = plan_count(P, rowptr, col, P.sort_keys, P.cap_units, pad, s);
+    if (st != COGDL_OK) return st;
+    if (P.sliced)
+        COGDL_LAUNCH("plan_emit", k_plan_emit<true>, blocks, kPlanBlock, s, rowptr, n, G, kb, P.slice_min,
+                     P.row_cuts, P.counters, P.block_sums, P.row_units, P.alt_units, P.units_tmp, P.sort_keys,
+                     P.split_rows, P.part_units);
+    else
+        COGDL_LAUNCH("plan_emit", k_plan_emit<false>, blocks, kPlanBlock, s, rowptr, n, G, 0, 0, nullptr,
+                     P.counters, P.block_sums, P.row_units, nullptr, P.units_tmp, P.sort_keys, P.split_rows,
                      P.part_units);
-    }
     uint32_t *order = P.sort_vals;                    // [cap]: final order
     uint32_t *ping_k = P.sort_keys + P.cap_units;     // [2 * cap] ping buffers
     uint32_t *ping_v = P.sort_vals + P.cap_units;
@@ -494,15 +445,10 @@ cogdl_status plan_build(Plan &P, const int32_t *rowptr, const int32_t *col, hipS
     const int bits = bits_for(pad);
     COGDL_HIP_TRY(radix_sort_pairs(P.sort_keys, nullptr, sorted, order, P.cap_units, bits, ping_k,
                                    ping_v, P.sort_ws, s));
-    if (P.sliced)
-        COGDL_LAUNCH("plan_lists", k_plan_lists, 1, 64, s, sorted, P.n_units_dev(), G, kTinyUnit, kb,
-                     P.lists_tbl, P.counters);
-    else
-        COGDL_LAUNCH("plan_split", k_plan_split, 1, 64, s, sorted, P.n_units_dev(), G, kTinyUnit,
-                     P.counters);
-    const int64_t gb = (P.cap_units + 255) / 256;
-    COGDL_LAUNCH("plan_gather", k_plan_gather, (unsigned)(gb < 8192 ? gb : 8192), 256, s,
-                 P.units_tmp, order, P.n_units_dev(), P.cap_units, P.units);
+    const int64_t gb = (P.cap_units + kFinishBlock - 1) / kFinishBlock;
+    COGDL_LAUNCH("plan_finish", k_plan_finish, (unsigned)(gb < 2048 ? gb : 2048), kFinishBlock, s, P.units_tmp,
+                 order, sorted, P.n_units_dev(), P.cap_units, G, kTinyUnit, (int)P.sliced, kb, P.lists_tbl,
+                 P.counters, P.units);
     return COGDL_OK;
 }
 
@@ -557,7 +503,7 @@ int32_t default_group(int32_t group_size, int64_t nnz)
     return G;
 }
 
-// The per-row arrays, counters and scan workspace: in the main allocation of
+// The per-row arrays, counters and workgroup sums: in the main allocation of
 // a plain plan, in base2 of a sliced one (which also holds the unsliced
 // counts and the list table), allocated first so that the creation can size
 // the rest from the sliced totals.
@@ -566,32 +512,27 @@ size_t row_layout(Plan &P, char *b, bool assign)
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align256(bytes); return o; };
     const size_t rows = 4 * ((size_t)P.n_rows + 1);
-    const size_t o_row_units = take(rows), o_row_parts = take(rows), o_row_split = take(rows);
-    const size_t o_counters = take(4 * 8);
-    P.scan_ws_bytes = scan_workspace_bytes(P.n_rows, 3);
-    const size_t o_scan_ws = take(P.scan_ws_bytes);
-    size_t o_alt = 0, o_tbl = 0, o_cuts = 0, o_tot = 0, o_btot = 0;
+    const size_t o_row_units = take(rows);
+    const size_t o_counters = take(4 * 16);
+    const size_t o_sums = take(4 * kPlanSums * (((size_t)P.n_rows + kPlanBlock - 1) / kPlanBlock + 1));
+    size_t o_alt = 0, o_tbl = 0, o_cuts = 0, o_tot = 0;
     if (P.sliced) {
-        o_alt = take(3 * rows);
+        o_alt = take(rows);
         o_tbl = take(4 * 3 * kSlices);
         o_cuts = take(4 * (kSlices - 1) * (size_t)P.n_rows);
         o_tot = take(8 * 3);
-        o_btot = take(8 * 3 * (((size_t)P.n_rows + 255) / 256 + 1));
     }
     if (assign) {
         P.row_units = reinterpret_cast<int32_t *>(b + o_row_units);
-        P.row_parts = reinterpret_cast<int32_t *>(b + o_row_parts);
-        P.row_split = reinterpret_cast<int32_t *>(b + o_row_split);
         P.counters = reinterpret_cast<int32_t *>(b + o_counters);
-        P.scan_ws = b + o_scan_ws;
+        P.n_parts = P.counters + 8;
+        P.n_split = P.counters + 9;
+        P.block_sums = reinterpret_cast<uint32_t *>(b + o_sums);
         if (P.sliced) {
             P.alt_units = reinterpret_cast<int32_t *>(b + o_alt);
-            P.alt_parts = P.alt_units + (P.n_rows + 1);
-            P.alt_split = P.alt_parts + (P.n_rows + 1);
             P.lists_tbl = reinterpret_cast<int32_t *>(b + o_tbl);
             P.row_cuts = reinterpret_cast<int32_t *>(b + o_cuts);
             P.totals = reinterpret_cast<unsigned long long *>(b + o_tot);
-            P.block_totals = reinterpret_cast<unsigned long long *>(b + o_btot);
         }
     }
     return off;
@@ -725,15 +666,7 @@ cogdl_status cogdl_plan_create_sliced(int32_t n_rows, int64_t nnz, const int32_t
     P.cap_partials = 2 * (nnz / G) + 2;
     if (n_rows > 0) {
         unsigned long long tot[3] = {0, 0, 0};
-        const unsigned blocks = (unsigned)((n_rows + 255) / 256);
-        cogdl_status st = COGDL_OK;
-        if (cogdl::fill_i32(P.counters, 8, 0, stream) != hipSuccess) st = COGDL_ERR_LAUNCH;
-        if (st == COGDL_OK) {
-            cogdl::k_plan_close<<<blocks < 512 ? blocks : 512, 256, 0, stream>>>(rowptr, n_rows, nnz,
-                                                                                  P.counters);
-            if (hipGetLastError() != hipSuccess) st = COGDL_ERR_LAUNCH;
-        }
-        if (st == COGDL_OK) st = cogdl::plan_counts_sliced(P, rowptr, col, stream);
+        cogdl_status st = cogdl::plan_count(P, rowptr, col, nullptr, 0, 0, stream);
         if (st == COGDL_OK &&
             (hipMemcpyAsync(&tot[0], P.totals, sizeof(tot), hipMemcpyDeviceToHost, stream) != hipSuccess ||
              hipStreamSynchronize(stream) != hipSuccess))
@@ -811,7 +744,7 @@ cogdl_status cogdl_plan_query(const cogdl_plan *plan, hipStream_t stream, cogdl_
                                : v[3];
     info->device_bytes = (int64_t)P.bytes;
     // the last build's rowptr held more edges than the plan was created for:
-    // the plan was left empty (see k_plan_check)
+    // the plan was left empty (see k_plan_totals)
     return (P.n_rows > 0 && v[5] != 0) ? COGDL_ERR_PLAN : COGDL_OK;
 }
 

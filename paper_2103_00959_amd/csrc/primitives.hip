@@ -1,7 +1,6 @@
-// Device-wide building blocks used by the balancer and the CSR -> CSC
-// transpose: an exclusive prefix sum and a stable least-significant-digit
-// radix sort of (key, value) pairs.  Both are deterministic (integer work,
-// fixed tile order); neither allocates.
+// Device-wide building block of the balancer and the CSR -> CSC transpose: a
+// stable least-significant-digit radix sort of (key, value) pairs.  It is
+// deterministic (integer work, fixed tile order) and does not allocate.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -9,116 +8,15 @@ namespace cogdl {
 
 namespace {
 
-constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
-constexpr int kScanTile = kScanBlock * kScanItems;   // 2048
+constexpr int kScanTile = 256 * kScanItems;          // 2048
+constexpr int kManyTiles = 2048;                     // the reserve holds kDigits totals from here on
 
 constexpr int kSortBlock = 256;                      // 4 wavefronts
 constexpr int kSortItems = 16;
 constexpr int kSortTile = kSortBlock * kSortItems;   // 4096
 constexpr int kDigits = 256;                         // digits of at most 8 bits
 constexpr int kMaxDigitBits = 8;                     // widest digit of a pass
-
-__device__ __forceinline__ int wave_inclusive_scan(int x)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int y = __builtin_amdgcn_ds_bpermute((lane >= d ? lane - d : lane) << 2, x);
-        if (lane >= d) x += y;
-    }
-    return x;
-}
-
-// Exclusive scan of one value per thread across a 256-thread block; returns
-// the exclusive prefix and writes the block total to *total.
-__device__ __forceinline__ int block_exclusive_scan(int x, int *total)
-{
-    __shared__ int wsum[kScanBlock / kWave];
-    const int lane = lane_id(), w = threadIdx.x / kWave;
-    int inc = wave_inclusive_scan(x);
-    if (lane == kWave - 1) wsum[w] = inc;
-    __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int i = 0; i < kScanBlock / kWave; ++i) {
-        if (i < w) before += wsum[i];
-        all += wsum[i];
-    }
-    __syncthreads();
-    *total = all;
-    return before + inc - x;
-}
-
-// K arrays scanned side by side (one launch for all of them); sums of the
-// tiles of array k at tile_sums[k * stride + tile].
-template <int K>
-struct ScanSet {
-    const int32_t *in[K];
-    int32_t *out[K];
-};
-
-template <int K>
-__global__ __launch_bounds__(kScanBlock) void k_tile_reduce(ScanSet<K> a, int64_t n,
-                                                            int32_t *__restrict__ tile_sums,
-                                                            int64_t stride)
-{
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        int s = 0;
-#pragma unroll
-        for (int i = 0; i < kScanItems; ++i)
-            if (base + i < n) s += a.in[k][base + i];
-        int total;
-        block_exclusive_scan(s, &total);
-        if (threadIdx.x == 0) tile_sums[k * stride + blockIdx.x] = total;
-    }
-}
-
-// Scan one tile of each array and add the tile's offset: tile_offs[k * stride +
-// tile] when given; else, with `sums` given, the sum of sums[k * stride + t]
-// over the tiles t before this one (added up by the block itself, so a scan
-// of up to kDirectTiles tiles needs no second level); else 0 (single tile).
-// The block holding the last element also writes out[n] = total.
-constexpr int64_t kDirectTiles = 8192;
-
-template <int K>
-__global__ __launch_bounds__(kScanBlock) void k_tile_scan(ScanSet<K> a, int64_t n,
-                                                          const int32_t *__restrict__ tile_offs,
-                                                          int64_t stride,
-                                                          const int32_t *__restrict__ sums)
-{
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        int before = 0;
-        if (!tile_offs && sums) {
-            int part = 0;
-            for (int t = threadIdx.x; t < (int)blockIdx.x; t += kScanBlock) part += sums[k * stride + t];
-            int all;
-            block_exclusive_scan(part, &all);
-            before = all;
-        }
-        int v[kScanItems];
-        int s = 0;
-#pragma unroll
-        for (int i = 0; i < kScanItems; ++i) {
-            v[i] = (base + i < n) ? a.in[k][base + i] : 0;
-            s += v[i];
-        }
-        int total;
-        int run = block_exclusive_scan(s, &total);   // contains a barrier: all reads done
-        const int off = tile_offs ? tile_offs[k * stride + blockIdx.x] : before;
-        run += off;
-#pragma unroll
-        for (int i = 0; i < kScanItems; ++i) {
-            if (base + i < n) a.out[k][base + i] = run;
-            run += v[i];
-        }
-        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) a.out[k][n] = off + total;
-    }
-}
 
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
 {
@@ -127,9 +25,40 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
         p[i] = v;
 }
 
+// Inclusive prefix sums of each digit's tile counts in place, one workgroup of WAVES
+// wavefronts per digit; the digit's total goes to totals[digit] as well when given (else
+// the scatter takes it from the row's last entry).  One launch between a pass's
+// histogram and its scatter, where a scan of the whole digit-major table took two.
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void k_digit_scan(int32_t *__restrict__ hist, int n_tiles,
+                                                              int32_t *__restrict__ totals)
+{
+    int32_t *__restrict__ row = hist + (int64_t)blockIdx.x * n_tiles;
+    int carry = 0;
+    for (int base = 0; base < n_tiles; base += WAVES * kWave * kScanItems) {
+        const int at = base + (int)threadIdx.x * kScanItems;
+        int v[kScanItems];
+        int s = 0;
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            v[i] = at + i < n_tiles ? row[at + i] : 0;
+            s += v[i];
+        }
+        int total;
+        int run = carry + block_exclusive_scan<WAVES>(s, &total);
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            run += v[i];
+            if (at + i < n_tiles) row[at + i] = run;
+        }
+        carry += total;
+    }
+    if (totals && threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
 // Per-tile histogram of one digit (bits [shift, shift + dbits) of the key),
-// stored digit-major so that an exclusive scan of the whole table yields every
-// (digit, tile) start slot.  Each wavefront counts into kHistCopies LDS copies
+// stored digit-major, so that the sums over a digit's tiles (k_digit_scan) and over the
+// digits before it (the scatter) give every (digit, tile) start slot.  Each wavefront counts into kHistCopies LDS copies
 // (lane % kHistCopies picks one), so the lanes of a wavefront that share a
 // digit, common on the high digits of power-law keys, collide on one LDS
 // address a quarter as often.
@@ -207,7 +136,8 @@ template <int NP, bool ROWS>
 __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
     const uint32_t *__restrict__ keys_in, const uint32_t *__restrict__ vals_in,
     uint32_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out, int64_t n, int shift,
-    int dbits, int n_tiles, const int32_t *__restrict__ offsets, RadixPayload p0, RadixPayload p1,
+    int dbits, int n_tiles, const int32_t *__restrict__ counts, const int32_t *__restrict__ totals,
+    int32_t tstride, RadixPayload p0, RadixPayload p1,
     const int32_t *__restrict__ start_rows)
 {
     constexpr int kWaves = kSortBlock / kWave;
@@ -257,7 +187,11 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
     }
     __syncthreads();
 
-    const uint64_t lower = __lanemask_lt();
+    // this thread's digit: its elements in all tiles, and in the tiles before this one
+    const bool used = tid <= (int)dmask;
+    const int digit_total = used ? totals[(int64_t)tid * tstride] : 0;
+    const int digit_before = used && tile > 0 ? counts[(int64_t)tid * n_tiles + tile - 1] : 0;
+    const uint64_t below = __lanemask_lt();
     int local[kSortItems];
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
@@ -271,7 +205,7 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
             const uint64_t m = __ballot(bit);
             peers &= bit ? m : ~m;
         }
-        const int rank = __popcll(peers & lower);
+        const int rank = __popcll(peers & below);
         int old = 0;
         if (valid) old = wcnt[w][d];
         local[i] = valid ? old + rank : -1;
@@ -283,10 +217,12 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
         int tot = 0;
 #pragma unroll
         for (int i = 0; i < kWaves; ++i) tot += wcnt[i][tid];
-        int all;
-        const int start = block_exclusive_scan(tot, &all);
+        // (beside it: the elements of lower digits; then those of this digit in the tiles before)
+        int first[2] = {tot, digit_total}, all[2];
+        block_exclusive_scans<2>(first, all);
+        const int start = first[0];
         dstart[tid] = start;
-        gstart[tid] = tid <= (int)dmask ? offsets[(int64_t)tid * n_tiles + tile] : 0;
+        gstart[tid] = first[1] + digit_before;
         int run = start;
 #pragma unroll
         for (int i = 0; i < kWaves; ++i) {
@@ -343,63 +279,9 @@ int64_t scan_levels_ints(int64_t n)
     return total;
 }
 
-template <int K>
-hipError_t scan_rec(ScanSet<K> a, int64_t n, int32_t *ws, hipStream_t s)
-{
-    if (n <= 0) {
-        for (int k = 0; k < K; ++k) COGDL_LAUNCH_HIP("fill", k_fill_i32, 1, 64, s, a.out[k], 1, 0);
-        return hipSuccess;
-    }
-    const int64_t tiles = (n + kScanTile - 1) / kScanTile;
-    if (tiles == 1) {
-        COGDL_LAUNCH_HIP("scan_tile", k_tile_scan<K>, 1, kScanBlock, s, a, n, nullptr, 0, nullptr);
-        return hipSuccess;
-    }
-    // the tile sums of array k at ws[k * (tiles + 1)], scanned in place
-    const int64_t stride = tiles + 1;
-    int32_t *sums = ws;
-    COGDL_LAUNCH_HIP("scan_reduce", k_tile_reduce<K>, (unsigned)tiles, kScanBlock, s, a, n, sums,
-                     stride);
-    if (tiles <= kDirectTiles) {
-        COGDL_LAUNCH_HIP("scan_tile", k_tile_scan<K>, (unsigned)tiles, kScanBlock, s, a, n, nullptr,
-                         stride, sums);
-        return hipSuccess;
-    }
-    ScanSet<K> b;
-    for (int k = 0; k < K; ++k) {
-        b.in[k] = sums + k * stride;
-        b.out[k] = sums + k * stride;
-    }
-    hipError_t e = scan_rec<K>(b, tiles, ws + K * stride, s);
-    if (e != hipSuccess) return e;
-    COGDL_LAUNCH_HIP("scan_tile", k_tile_scan<K>, (unsigned)tiles, kScanBlock, s, a, n, sums, stride,
-                     nullptr);
-    return hipSuccess;
-}
+size_t scan_reserve_bytes(int64_t n) { return (size_t)(scan_levels_ints(n) + 16) * 4; }
 
 }  // namespace
-
-size_t scan_workspace_bytes(int64_t n, int arrays)
-{
-    return (size_t)(arrays * scan_levels_ints(n) + 16) * 4;
-}
-
-hipError_t exclusive_scan(const int32_t *in, int32_t *out, int64_t n, void *ws, hipStream_t s)
-{
-    ScanSet<1> a;
-    a.in[0] = in;
-    a.out[0] = out;
-    return scan_rec<1>(a, n, static_cast<int32_t *>(ws), s);
-}
-
-hipError_t exclusive_scan3(int32_t *a0, int32_t *a1, int32_t *a2, int64_t n, void *ws, hipStream_t s)
-{
-    ScanSet<3> a;
-    a.in[0] = a.out[0] = a0;
-    a.in[1] = a.out[1] = a1;
-    a.in[2] = a.out[2] = a2;
-    return scan_rec<3>(a, n, static_cast<int32_t *>(ws), s);
-}
 
 hipError_t fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s)
 {
@@ -410,15 +292,17 @@ hipError_t fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s)
     return hipSuccess;
 }
 
-// Workspace of a radix sort of n keys: the digit table (+ its scan's scratch)
-// and one start row per wavefront of a tile (rows generated from rowptr).
+// Workspace of a radix sort of n keys: the digit table, a reserve of one int per 2048 of
+// its entries (level by level: the sizes callers allocate by, and the graphs the
+// allocation-free transpose accepts, depend on the total), and one start row per
+// wavefront of a tile (rows generated from rowptr).
 size_t radix_workspace_bytes(int64_t n)
 {
     const int64_t tiles = (n + kSortTile - 1) / kSortTile;
     const int64_t hist = (int64_t)kDigits * (tiles > 0 ? tiles : 1) + 1;
     size_t b = (size_t)(hist + 64) * 4;
     b = (b + 255) & ~size_t(255);
-    b += (scan_workspace_bytes(hist) + 255) & ~size_t(255);
+    b += (scan_reserve_bytes(hist) + 255) & ~size_t(255);
     return b + (size_t)(tiles > 0 ? tiles : 1) * (kSortBlock / kWave) * 4;
 }
 
@@ -433,9 +317,9 @@ hipError_t radix_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, ui
     const int64_t hist_n = (int64_t)kDigits * tiles;
     int32_t *hist = static_cast<int32_t *>(ws);
     size_t hist_bytes = ((size_t)(hist_n + 1 + 64) * 4 + 255) & ~size_t(255);
-    void *scan_ws = static_cast<char *>(ws) + hist_bytes;
+    int32_t *reserve = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + hist_bytes);
     int32_t *start_rows = reinterpret_cast<int32_t *>(
-        static_cast<char *>(scan_ws) + ((scan_workspace_bytes(hist_n + 1) + 255) & ~size_t(255)));
+        static_cast<char *>(ws) + hist_bytes + ((scan_reserve_bytes(hist_n + 1) + 255) & ~size_t(255)));
 
     // as few passes as digits of at most 8 bits allow, the bits spread evenly
     // over them (longer runs per digit than a short last pass gives), a
@@ -459,14 +343,20 @@ hipError_t radix_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, ui
         pa.rowptr = pay0.rowptr;
         pa.n_rows = pay0.n_rows;
         RadixPayload pb{b.in, last ? pay1.out : (pay1.ping ? pay1.ping + (p & 1) * n : nullptr), nullptr};
-        const int64_t used = (int64_t)(1 << dbits) * tiles;
         COGDL_LAUNCH_HIP("radix_hist", k_radix_hist, (unsigned)tiles, kSortBlock, s, src_k, n, shift,
                          dbits, (int)tiles, hist, pay0.rowptr, pay0.n_rows, rows ? start_rows : nullptr);
-        hipError_t e = exclusive_scan(hist, hist, used, scan_ws, s);
-        if (e != hipSuccess) return e;
+        // many tiles: wider scans, and the totals side by side where the workspace's reserve
+        // holds them (122M elements: the transpose takes 3.26 ms without either, 3.18 with)
+        if (tiles >= kManyTiles)
+            COGDL_LAUNCH_HIP("radix_scan", k_digit_scan<16>, 1u << dbits, 16 * kWave, s, hist, (int)tiles, reserve);
+        else
+            COGDL_LAUNCH_HIP("radix_scan", k_digit_scan<4>, 1u << dbits, 4 * kWave, s, hist, (int)tiles,
+                             (int32_t *)nullptr);
+        const int32_t *totals = tiles >= kManyTiles ? reserve : hist + (tiles - 1);
+        const int32_t tstride = tiles >= kManyTiles ? 1 : (int32_t)tiles;
 #define COGDL_SCATTER(NPV, ROWSV)                                                                \
     COGDL_LAUNCH_HIP("radix_scatter", (k_radix_scatter<NPV, ROWSV>), (unsigned)tiles, kSortBlock, s, \
-                     src_k, src_v, dst_k, dst_v, n, shift, dbits, (int)tiles, hist, pa, pb,          \
+                     src_k, src_v, dst_k, dst_v, n, shift, dbits, (int)tiles, hist, totals, tstride, pa, pb, \
                      start_rows)
         if (np == 0) COGDL_SCATTER(0, false);
         else if (np == 1 && rows) COGDL_SCATTER(1, true);
