@@ -128,8 +128,18 @@ inline int64_t list_grid(int64_t blocks, int lists)
 const Plan *plan_of(const cogdl_plan *h);
 
 // Workgroups of `block` threads of `kernel` with `shm` bytes of dynamic LDS that fit on
-// the device at once (all compute units), cached per kernel and shm.
-int resident_blocks(const void *kernel, int block, size_t shm = 0);
+// the device at once (all compute units), at most `most` a compute unit when given;
+// cached per kernel, shm and most.
+int resident_blocks(const void *kernel, int block, size_t shm = 0, int most = 0);
+
+// Workgroups a compute unit of the gathers over tables past the Infinity Cache (256 MB):
+// with the fourth one the rows in flight evict more of what the L2s would serve.  SpMM
+// with rows of 512 bytes and more, 122M edges x 256 bf16: 5.30 ms, with three 5.12 (60M
+// fp32 rows of 512 bytes 0.96 and 0.94; rows of 256 bytes 1.27 and 1.32, so not there).
+// Aggregation on given scores, 60M edges: 4 x 64 bf16 3.34 and 3.23, 8 x 16 fp32 3.30
+// and 3.25, 4 x 32 bf16 1.83 and 1.77.  Tables the caches hold want every wavefront.
+constexpr uint64_t kCachedTable = 256ull << 20;
+constexpr int kFarTableBlocks = 3;
 
 // Y[row] = sum of the partial rows of every split row of the plan (F columns),
 // divided by the row's degree when `mean`, then act(. + bias) when given.

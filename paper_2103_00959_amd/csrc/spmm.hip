@@ -257,7 +257,8 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
         SpmmKernel k = pick(m.ch);
         if (!k) return COGDL_ERR_DTYPE;
         int64_t blocks = (units + upb - 1) / upb;
-        const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock);
+        const bool far = !maxr && (int64_t)F * dtype_bytes(xdt) >= 512 && a.x_bytes > kCachedTable;
+        const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock, 0, far ? kFarTableBlocks : 0);
         if (blocks > res) blocks = res;
         blocks = list_grid(blocks, a.lists);
         COGDL_LAUNCH(names.main, k, dim3((unsigned)blocks, (unsigned)m.n_slabs), kBlock, s, a);

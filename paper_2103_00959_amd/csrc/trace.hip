@@ -62,16 +62,17 @@ void trace_end(int slot, hipStream_t s)
     if (slot >= 0) (void)hipEventRecord(g_trace.stop[slot], s);
 }
 
-int resident_blocks(const void *kernel, int block, size_t shm)
+int resident_blocks(const void *kernel, int block, size_t shm, int most)
 {
-    struct Entry { const void *kernel; size_t shm; int device, block, blocks; };
+    struct Entry { const void *kernel; size_t shm; int device, block, most, blocks; };
     static std::mutex mu;
     static std::vector<Entry> cache;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return 2048; }
     std::lock_guard<std::mutex> lock(mu);
     for (const Entry &e : cache)
-        if (e.kernel == kernel && e.device == dev && e.block == block && e.shm == shm) return e.blocks;
+        if (e.kernel == kernel && e.device == dev && e.block == block && e.shm == shm && e.most == most)
+            return e.blocks;
     int cus = 0, per_cu = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, shm) != hipSuccess ||
@@ -79,7 +80,8 @@ int resident_blocks(const void *kernel, int block, size_t shm)
         (void)hipGetLastError();
         return 2048;
     }
-    cache.push_back(Entry{kernel, shm, dev, block, cus * per_cu});
+    if (most > 0 && per_cu > most) per_cu = most;
+    cache.push_back(Entry{kernel, shm, dev, block, most, cus * per_cu});
     return cus * per_cu;
 }
 
