@@ -225,6 +225,7 @@ struct RowMap {
 // 33 bf16 2.08 against 2.81, 7 fp32 1.38 against 1.52), rows off the 64-byte grid
 // costing more requests as vectors than as lanes.
 RowMap span_map(int64_t width, int elem_bytes);
+RowMap element_map(int64_t width);      // one element per lane
 
 // Geometry of k_gat for H heads of D features: 16-byte vectors at any alignment (one
 // element per lane for heads narrower than a vector), L slots per head (k_gat), S lanes

@@ -404,6 +404,8 @@ RowMap span_map(int64_t width, int elem_bytes)
     return lane_map(width, width >= v16 && !ragged ? v16 : 1);
 }
 
+RowMap element_map(int64_t width) { return lane_map(width, 1); }
+
 HeadMap head_map(int H, int D, int elem_bytes)
 {
     HeadMap m;

@@ -25,6 +25,23 @@ namespace {
 
 constexpr int kBlock = kSpmmBlock;
 
+// Whether the units of a sum run a wavefront each (k_spmm_wave) instead of a group of S
+// lanes.  With a plan: while the units are few enough that the call takes as long as its
+// longest unit, a chain of gathers.  Forward and backward, us, group / wavefront: 12k rows
+// and 100k edges, 64 bf16 62 / 35, 256 bf16 72 / 49; 50k and 500k 95 / 73, 93 / 87; 50k and
+// 2.5M (60k units) 102 / 96, 163 / 178; 100k and 500k 100 / 124.  Rows of under 8 lanes take
+// several edges side by side anyway (16 bf16: 12k rows 35 / 35, 24k 35 / 46).  Without a plan
+// a hub row is one unit, so the chain is far longer (50k rows, 2.5M edges, 64 bf16: 2299 /
+// 524; 169k and 2.5M, 256 bf16: 2400 / 1495), but a graph of even rows loses what their
+// lanes leave empty: there also where the mean row fills half a step's slots (8 slots of
+// 64 / S edges).
+bool unit_per_wave(bool plan, int S, int64_t units, int64_t nnz)
+{
+    if (S >= kWave) return false;
+    if (units <= (S < 8 ? 8192 : plan ? 55000 : 16384)) return true;
+    return !plan && nnz >= units * (256 / S);
+}
+
 // Y[row, :] = sum of the row's partial rows (times 1 / degree for mean).  A
 // wavefront per split row (grid-stride over the device-side count, uniform
 // per wavefront), VEC features per lane: slot g goes to chain g mod 4, the
@@ -215,7 +232,19 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     if (P && (P->n_rows != out_rows || P->nnz != nnz || P->max_feat < F)) return COGDL_ERR_PLAN;
     if (out_rows == 0 || F == 0) return COGDL_OK;
 
-    const RowMap m = span_map(F, dtype_bytes(xdt));
+    RowMap m = span_map(F, dtype_bytes(xdt));
+    const int64_t units = P ? P->cap_units : out_rows;
+    const bool sums = !maxr && compute != COGDL_COMPUTE_ADD && compute != COGDL_COMPUTE_SUB;
+    const bool offsets = sums && (uint64_t)in_rows * (uint64_t)F * (uint64_t)dtype_bytes(xdt) <= kMaskedOffset;
+    // Ragged rows of 33 to 64 elements on 8 lanes make longer chains than on 64 element
+    // lanes (8 edges a step against 16): without a plan, and on graphs of middle size
+    // with short rows, they keep those (41 bf16, us, elements / vectors: 100k rows and
+    // 500k edges 69 / 112, 50k and 500k 60 / 79, 169k without a plan 1227 / 2627; but 100k
+    // and 2M 130 / 130, 24k and 200k 48 / 45).
+    if (m.vec > 1 && m.S == 8 && F % m.vec != 0 && !(offsets && unit_per_wave(P != nullptr, m.S, units, nnz) &&
+                                                     (units <= 32768 || !P)) &&
+        (!P || (units > 32768 && units <= 131072 && nnz < 16 * (int64_t)out_rows)))
+        m = element_map(F);
     SpmmArgs a;
     a.units = P ? P->units : nullptr;
     a.u_lo = nullptr;
@@ -241,20 +270,20 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     const bool addop = compute == COGDL_COMPUTE_ADD || compute == COGDL_COMPUTE_SUB;
     const bool buf = a.x_bytes <= kBufferMaxBytes;
     // sums over rows of at most four lanes: several edges of a unit side by side
-    const bool narrow = a.x_bytes <= kMaskedOffset && !maxr && !addop && m.S < 8;
+    const bool narrow = offsets && m.S < 8;
     auto pick = [&](int ch) {
         return (maxr || addop) ? gspmm_pick(maxr, addop, xdt, ydt, m.vec, ch, buf)
                : narrow        ? narrow_pick(xdt, ydt, m.vec, m.S)
                                : spmm_pick<false, false>(xdt, ydt, m.vec, ch, buf);
     };
-    const int64_t units = P ? P->cap_units : out_rows;
     // Units of at most kTinyUnit edges (the sorted tail) run with S/4 lanes and
     // four chunks per lane: four times as many rows in flight per wavefront.
-    const bool tiny = P && m.ch == 1 && m.S >= 8;
+    const bool wave = offsets && m.ch == 1 && unit_per_wave(P != nullptr, m.S, units, nnz);
+    const bool tiny = P && m.ch == 1 && m.S >= 8 && !wave;
     if (P) set_units(a, tiny ? long_units(*P) : all_units(*P));
     {
-        const int64_t upb = narrow ? kBlock / 8 : kBlock >> m.log2S;
-        SpmmKernel k = pick(m.ch);
+        const int64_t upb = wave ? kBlock / kWave : narrow ? kBlock / 8 : kBlock >> m.log2S;
+        SpmmKernel k = wave ? wave_pick(xdt, ydt, m.vec) : pick(m.ch);
         if (!k) return COGDL_ERR_DTYPE;
         int64_t blocks = (units + upb - 1) / upb;
         const bool far = !maxr && (int64_t)F * dtype_bytes(xdt) >= 512 && a.x_bytes > kCachedTable;

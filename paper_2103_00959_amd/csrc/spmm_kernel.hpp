@@ -331,7 +331,95 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm_narrow(SpmmArgs a)
     }
 }
 
+// Sum of products with a wavefront per unit, for graphs of few units (unit_per_wave): there
+// a call takes as long as its longest unit, a chain of batches of gathers, one memory
+// latency each, so the wavefront's 64 / 2^log2S edge slots (lane = slot * 2^log2S +
+// vector of the row) take the unit's edges side by side, 8 gathers in flight a lane, and
+// their sums are added across lanes at the end.  Rows of one slab and one chunk per lane.
+template <typename TX, typename TY, int VEC>
+__global__ __launch_bounds__(kSpmmBlock) void k_spmm_wave(SpmmArgs a)
+{
+    constexpr int U = 8;
+    const int lane = lane_id();
+    const int LQ = 1 << a.log2S, EP = kWave >> a.log2S;
+    const int q = lane & (LQ - 1), slot = lane >> a.log2S;
+    const UnitWalk walk = unit_walk(a.units != nullptr, a.u_lo, a.u_hi, a.lists, a.n_rows, kSpmmBlock / kWave,
+                                    threadIdx.x / kWave);
+    const int64_t hi = walk.end;
+    int64_t fe = (int64_t)q * VEC;
+    const bool act = fe < a.F;
+    if (act && fe + VEC > a.F) fe = a.F - VEC;       // the row's last vector (see k_spmm)
+    const RowGather<TX, VEC, true> X(a.X, a.x_bytes);
+    const uint32_t row_bytes = (uint32_t)a.F * (uint32_t)sizeof(TX);
+    const uint32_t lane_off = act ? (uint32_t)fe * (uint32_t)sizeof(TX) : 0u;
+    const uint32_t lane_min = act ? 0u : kMaskedOffset;
+    for (int64_t u = walk.first; u < hi; u += walk.step) {
+        const int4 d = fetch_unit(a, u, hi);
+        const int row = d.x, beg = d.y, end = d.z, part = d.w;
+        float acc[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
+        for (int k0 = beg; k0 < end; k0 += kWave) {
+            const int n = (end - k0 < kWave) ? end - k0 : kWave;
+            // row offset and weight of edge k0 + lane (past the unit: past the buffer, 0)
+            const bool in = lane < n;
+            const int k = in ? k0 + lane : end - 1;
+            const uint32_t o_cur = in ? (uint32_t)a.col[k] * row_bytes : kMaskedOffset;
+            const float v_cur = in ? (a.val ? a.val[k] : 1.f) : 0.f;
+            for (int j = 0; j < n; j += U * EP) {
+                float xv[U][VEC], vv[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) {
+                    const int src = j + t * EP + slot;
+                    const bool inside = src < kWave;               // (fewer than 8 lanes a row)
+                    const uint32_t o = (uint32_t)lane_bcast((int)o_cur, src);
+                    const uint32_t off = (inside ? o : kMaskedOffset) + lane_off;
+                    const float v = lane_bcast(v_cur, src);
+                    vv[t] = inside ? v : 0.f;
+                    X.load_off(off > lane_min ? off : lane_min, xv[t]);
+                }
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vv[t], xv[t][e], acc[e]);
+            }
+        }
+        for (int off = LQ; off < kWave; off <<= 1)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[e] += lane_xor(acc[e], off);
+        if (slot == 0 && act) {
+            if (part < 0) {
+                if (a.mean && end > beg) {
+                    const float r = 1.f / (float)(end - beg);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) acc[e] *= r;
+                }
+                epilogue<VEC>(acc, a.bias, a.act, fe);
+                store_out<TY, VEC>(static_cast<TY *>(a.Y), (int64_t)row * a.F + fe, acc);
+            } else {
+                store_vec<float, VEC>(a.partials, (int64_t)part * a.pstride + fe, acc);
+            }
+        }
+    }
+}
+
 using SpmmKernel = void (*)(SpmmArgs);
+
+template <typename TX>
+SpmmKernel wave_pick_y(int ydt, int vec)
+{
+    constexpr int V = (int)(16 / sizeof(TX));
+    if (ydt == COGDL_F32) return vec == 1 ? k_spmm_wave<TX, float, 1> : k_spmm_wave<TX, float, V>;
+    if (ydt == COGDL_BF16) return vec == 1 ? k_spmm_wave<TX, bf16_t, 1> : k_spmm_wave<TX, bf16_t, V>;
+    return vec == 1 ? k_spmm_wave<TX, f16_t, 1> : k_spmm_wave<TX, f16_t, V>;
+}
+
+inline SpmmKernel wave_pick(int xdt, int ydt, int vec)
+{
+    if (xdt == COGDL_F32) return wave_pick_y<float>(ydt, vec);
+    if (xdt == COGDL_BF16) return wave_pick_y<bf16_t>(ydt, vec);
+    return wave_pick_y<f16_t>(ydt, vec);
+}
 
 template <typename TX, typename TY>
 SpmmKernel narrow_pick_lq(int vec, int lq)

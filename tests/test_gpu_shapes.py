@@ -107,6 +107,27 @@ def test_spmm_odd_widths_and_alignment(cg, F, xk, yk):
                 _untouched(abuf, g.n_rows * F, by)
 
 
+@pytest.mark.parametrize("F", [3, 8, 16, 24, 33, 41, 65, 128])
+@pytest.mark.parametrize("xk", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [9000, 60000])
+def test_spmm_past_the_unit_limits(cg, F, xk, n):
+    """The same sums with more units than run a wavefront each (8192 for narrow rows, 55000
+    with a plan, 16384 without)."""
+    g = _graph(F, n=n, m=3000)
+    say(f"spmm n={n} F={F} {xk}")
+    rp, cl, vl = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, F), 11 + F, xk)
+    Yr, Ar = oracle.spmm(g.rowptr, g.col, g.val, xh, x_dtype=xc)
+    deg = np.maximum(np.diff(g.rowptr), 1)[:, None]
+    for plan in _plans(cg, rp, cl, g, F):
+        out, buf = _guarded((g.n_rows, F), xd.dtype, 0)
+        cg.spmm(rp, cl, vl, xd, plan=plan, out=out)
+        assert scaled_error(out, Yr, Ar) <= tol_for(xk, xk), (F, xk, n)
+        _untouched(buf, g.n_rows * F, 0)
+        out = cg.gspmm(rp, cl, vl, xd, "mean", plan=plan)
+        assert scaled_error(out, Yr / deg, Ar / deg) <= tol_for(xk, xk), (F, xk, n, "mean")
+
+
 # one head of an odd width; heads below a vector; groups of 1, 2, 4 and 8 owner lanes; heads past one
 # wavefront (slabs, the last one part full); more heads than lanes a head; a head too wide for the map
 HEADS = [(1, 41, "bf16"), (1, 8, "bf16"), (2, 9, "f16"), (3, 17, "bf16"), (1, 5, "bf16"), (2, 3, "f32"), (4, 32, "bf16"),
