@@ -34,10 +34,11 @@ constexpr int kBlock = kSpmmBlock;
 // a hub row is one unit, so the chain is far longer (50k rows, 2.5M edges, 64 bf16: 2299 /
 // 524; 169k and 2.5M, 256 bf16: 2400 / 1495), but a graph of even rows loses what their
 // lanes leave empty: there also where the mean row fills half a step's slots (8 slots of
-// 64 / S edges).
-bool unit_per_wave(bool plan, int S, int64_t units, int64_t nnz)
+// 64 / S edges).  Neighbour groups of under 64 edges are no chains and keep their groups.
+bool unit_per_wave(const Plan *plan, int S, int64_t units, int64_t nnz)
 {
     if (S >= kWave) return false;
+    if (plan && plan->mode_req == COGDL_BALANCE_NEIGHBOR_GROUP && plan->group_size < kWave) return false;
     if (units <= (S < 8 ? 8192 : plan ? 55000 : 16384)) return true;
     return !plan && nnz >= units * (256 / S);
 }
@@ -241,7 +242,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     // with short rows, they keep those (41 bf16, us, elements / vectors: 100k rows and
     // 500k edges 69 / 112, 50k and 500k 60 / 79, 169k without a plan 1227 / 2627; but 100k
     // and 2M 130 / 130, 24k and 200k 48 / 45).
-    if (m.vec > 1 && m.S == 8 && F % m.vec != 0 && !(offsets && unit_per_wave(P != nullptr, m.S, units, nnz) &&
+    if (m.vec > 1 && m.S == 8 && F % m.vec != 0 && !(offsets && unit_per_wave(P, m.S, units, nnz) &&
                                                      (units <= 32768 || !P)) &&
         (!P || (units > 32768 && units <= 131072 && nnz < 16 * (int64_t)out_rows)))
         m = element_map(F);
@@ -278,7 +279,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     };
     // Units of at most kTinyUnit edges (the sorted tail) run with S/4 lanes and
     // four chunks per lane: four times as many rows in flight per wavefront.
-    const bool wave = offsets && m.ch == 1 && unit_per_wave(P != nullptr, m.S, units, nnz);
+    const bool wave = offsets && m.ch == 1 && unit_per_wave(P, m.S, units, nnz);
     const bool tiny = P && m.ch == 1 && m.S >= 8 && !wave;
     if (P) set_units(a, tiny ? long_units(*P) : all_units(*P));
     {

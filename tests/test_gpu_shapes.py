@@ -60,7 +60,7 @@ def _untouched(buf, n, by):
 
 def _plans(cg, rp, cl, g, width, heads=0):
     yield None
-    for kw in ({"mode": "neighbor_group", "group_size": 40}, {"mode": "neighbor_group", "group_size": 40, "col": cl,
+    for kw in ({"mode": "neighbor_group", "group_size": 40}, {"mode": "neighbor_group", "group_size": 64}, {"mode": "neighbor_group", "group_size": 40, "col": cl,
                                                               "n_cols": g.n_cols, "slice_min": 30}):
         p = cg.Plan(rp, g.nnz, max_feat=width, max_heads=heads, **kw)
         try:
