@@ -9,6 +9,8 @@
 // activation are applied before the single store.  The layers are tall and
 // skinny (k, m at most a few hundred, n in the millions): X is streamed once
 // per column block through LDS in 64-k chunks, W comes from the caches.
+// From 2048 rows on, where all of W fits LDS, W stays there and X goes straight
+// into the matrix operands instead (k_linear_stream).
 //
 // cogdl_head_scores: lanes over the features of a node's heads, a butterfly
 // for each head's two dot products (several nodes per wavefront when the

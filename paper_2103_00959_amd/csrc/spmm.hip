@@ -8,6 +8,9 @@
 //     a sub-group of S lanes; S lanes times VEC elements cover one feature row
 //     (S = 32 for a 512-byte row read as 16-byte vectors), CH chunks when the
 //     row is wider than 64 vectors, feature slabs beyond that.
+//     Rows of fewer than 8 lanes put several edges side by side (k_spmm_narrow);
+//     where the longest unit's chain of gathers sets the time, a unit has a
+//     whole wavefront (k_spmm_wave, rule at unit_per_wave).
 //   - The sub-group reads the unit's column indices and edge values S at a
 //     time with one coalesced load, prefetching the next S while it works, and
 //     hands them to every lane with ds_bpermute.
