@@ -559,12 +559,17 @@ cogdl_status cogdl_linear(int64_t n, int32_t k, int32_t m, const void *X, const 
         StreamArgs s{a, ny, slots, row16};
         StreamKernel kern = dtype == COGDL_BF16 ? pick_stream<bf16_t>((int)y_dtype, nt)
                                                 : pick_stream<f16_t>((int)y_dtype, nt);
-        // resident workgroups (as many as their LDS allows), a multiple of 8 for each column block
+        // gx workgroups for each of the ny column blocks, a multiple of 8: as many as the rows need,
+        // within the resident ones rounded down (rounded up, 3 column blocks of 88 were 264
+        // workgroups on 256 places and a second round for 8 of them: on 233k rows 48 -> 300 took
+        // 119 us, now 75, 602 -> 300 312 and 200), and at least 8: outputs wider than 128 times
+        // the resident workgroups take several rounds.
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(kern), kStreamBlock, lds);
         if (res < 1) return COGDL_ERR_LAUNCH;
-        int64_t gx = ((n + 31) / 32 + kStreamBlock / kWave - 1) / (kStreamBlock / kWave);
-        if (gx > res / ny) gx = res / ny;
-        gx = (gx + 7) / 8 * 8;
+        const int64_t need = (n + 32 * (kStreamBlock / kWave) - 1) / (32 * (kStreamBlock / kWave));
+        int64_t gx = res / ny / 8 * 8;
+        if (gx < 8) gx = 8;
+        if (gx > (need + 7) / 8 * 8) gx = (need + 7) / 8 * 8;
         COGDL_LAUNCH_SHM("linear", kern, dim3((unsigned)(gx * ny)), kStreamBlock, lds, stream, s);
         return COGDL_OK;
     }

@@ -317,3 +317,21 @@ def test_linear_streamed_shapes(cg, k, m, n, xk, yk):
         # fp32 accumulation of exact products: k 2^-24 of the terms' sum at most; fp16 also rounds the result
         assert scaled_error(out, Yr, Ar) <= k * 2.0 ** -24 + (0 if yk == "f32" else 1e-6), (k, m, n, by)
         _untouched(buf, n * m, by)
+
+
+@pytest.mark.parametrize("n,k,m", [(2048, 48, 32768), (2048, 48, 32769), (2081, 620, 33000), (4096, 512, 40000),
+                                   (30001, 48, 300), (30001, 602, 300), (70001, 64, 129)])
+def test_linear_grids(cg, n, k, m):
+    """The streaming kernel's grid: column blocks as many as the resident workgroups and more, three
+    and two of them over more row tiles than one round takes."""
+    import torch
+    say(f"linear n={n} k={k} m={m}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k + m)
+    x = torch.randn((n, k), device="cuda", generator=g).to(torch.bfloat16)
+    w = torch.randn((m, k), device="cuda", generator=g).to(torch.bfloat16)
+    y = cg.linear(x, w, out_dtype=torch.float32)
+    for r0 in range(0, n, 4096):
+        rows = x[r0:r0 + 4096].double()
+        bound = rows.abs() @ w.double().abs().T * (k * 2.0 ** -24)   # fp32 sums of exact products
+        assert torch.all((y[r0:r0 + 4096].double() - rows @ w.double().T).abs() <= bound), (n, k, m, r0)
