@@ -552,10 +552,9 @@ cogdl_status cogdl_linear(int64_t n, int32_t k, int32_t m, const void *X, const 
     const size_t lds = (size_t)32 * nt * row16 * 16 + 32 * nt * sizeof(float);
     const int ny = (m + 32 * nt - 1) / (32 * nt);
     // The streaming kernel from 2048 rows on where W fits in LDS: 602 -> 128 bf16 on 2.7k /
-    // 233k rows 30 -> 22 and 133 -> 101 us, 128 -> 48 31 -> 23, 135 -> 256 (odd rows) 189 -> 72.
-    // Short rows with wide outputs (24 -> 300: 100 against 113 us) stay with k_linear, whose
-    // stores cover 64 bytes of a row instead of 32.
-    if (k >= 8 && lds <= kStreamLds && n >= kStreamMinRows && (k >= 48 || m <= 128)) {
+    // 233k rows 30 -> 22 and 133 -> 101 us, 128 -> 48 31 -> 23, 135 -> 256 (odd rows) 189 -> 72,
+    // 24 -> 300 87 -> 72, 47 -> 1024 355 -> 196 (at worst 8 and 24 -> 300 on 30k rows 16 -> 17).
+    if (k >= 8 && lds <= kStreamLds && n >= kStreamMinRows) {
         StreamArgs s{a, ny, slots, row16};
         StreamKernel kern = dtype == COGDL_BF16 ? pick_stream<bf16_t>((int)y_dtype, nt)
                                                 : pick_stream<f16_t>((int)y_dtype, nt);

@@ -320,7 +320,8 @@ def test_linear_streamed_shapes(cg, k, m, n, xk, yk):
 
 
 @pytest.mark.parametrize("n,k,m", [(2048, 48, 32768), (2048, 48, 32769), (2081, 620, 33000), (4096, 512, 40000),
-                                   (30001, 48, 300), (30001, 602, 300), (70001, 64, 129)])
+                                   (30001, 48, 300), (30001, 602, 300), (70001, 64, 129),
+                                   (30001, 24, 300), (2081, 9, 401), (2048, 47, 1025), (2048, 8, 129)])
 def test_linear_grids(cg, n, k, m):
     """The streaming kernel's grid: column blocks as many as the resident workgroups and more, three
     and two of them over more row tiles than one round takes."""
