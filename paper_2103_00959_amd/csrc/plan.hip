@@ -77,16 +77,17 @@ constexpr int kPlanSums = 8;
 // the pad keys of the sort.  A sliced row (more than slice_min edges) gives ceil(len /
 // G) units per nonempty slice, its cuts stored for k_plan_emit; alt_units keeps the
 // unsliced count, which the build falls back to when the sliced totals exceed the
-// plan's capacities.
+// plan's capacities.  With `mode` given no row is sliced when it is row split.
 template <bool SLICED>
 __global__ __launch_bounds__(kPlanBlock) void k_plan_counts(
     const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int32_t n_rows, int64_t nnz, int32_t G,
-    int64_t width, int32_t slice_min, int32_t *__restrict__ row_units, int32_t *__restrict__ alt_units,
-    int32_t *__restrict__ row_cuts, uint32_t *__restrict__ sums, uint32_t *__restrict__ keys, int64_t n_keys,
+    int64_t width, int32_t slice_min, const int32_t *__restrict__ mode, int32_t *__restrict__ row_units,
+    int32_t *__restrict__ alt_units, int32_t *__restrict__ row_cuts, uint32_t *__restrict__ sums, uint32_t *__restrict__ keys, int64_t n_keys,
     uint32_t pad)
 {
     for (int64_t k = (int64_t)blockIdx.x * kPlanBlock + threadIdx.x; k < n_keys; k += (int64_t)gridDim.x * kPlanBlock)
         keys[k] = pad;
+    if (SLICED && mode && *mode == COGDL_BALANCE_ROW_SPLIT) slice_min = INT32_MAX;
     const int i = blockIdx.x * kPlanBlock + threadIdx.x;
     uint32_t v[7] = {0, 0, 0, 0, 0, 0, 0};
     if (i < n_rows) {
@@ -385,26 +386,38 @@ __global__ void k_plan_export(const int4 *__restrict__ units, const int32_t *__r
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
 // The row counts and totals of a rowptr (keys: the sort's keys to pad, or none).
+// Searching the cuts of long rows costs more than the rest of the count, and a row-split
+// plan has no use for them.  Where the mean degree is slice_min or more, the rows to cut
+// can be most rows of a balanced graph, so the mode is found first, by a plain count and
+// its totals (a rebuild of 200k rows of 300: 244 us with every cut searched, 79 now, 106
+// before the counting passes were merged); it costs a skewed graph two launches, 11 us.
+// Below, row split leaves few rows to cut in vain.
 cogdl_status plan_count(Plan &P, const int32_t *rowptr, const int32_t *col, uint32_t *keys, int64_t n_keys,
                         uint32_t pad, hipStream_t s)
 {
     const int n = P.n_rows;
     const unsigned blocks = (unsigned)((n + kPlanBlock - 1) / kPlanBlock);
-    if (P.sliced) {
-        const int64_t width = ((int64_t)P.n_cols + kSlices - 1) / kSlices;
-        // (a row-split plan asked for by the caller is never sliced)
-        const int32_t slice_min = P.mode_req == COGDL_BALANCE_ROW_SPLIT ? INT32_MAX : P.slice_min;
-        COGDL_LAUNCH("plan_counts", k_plan_counts<true>, blocks, kPlanBlock, s, rowptr, col, n, P.nnz,
-                     P.group_size, width > 0 ? width : 1, slice_min, P.row_units, P.alt_units, P.row_cuts,
-                     P.block_sums, keys, n_keys, pad);
-    } else {
+    const auto totals = [&](int sliced) -> cogdl_status {
+        COGDL_LAUNCH("plan_totals", k_plan_totals, 1, kTotalsBlock, s, P.block_sums, (int64_t)blocks, n,
+                     (int)P.mode_req, sliced, P.cap_units, P.cap_partials, P.cap_split, sliced ? P.totals : nullptr,
+                     P.row_units + n, P.n_parts, P.n_split, P.counters);
+        return COGDL_OK;
+    };
+    const bool mode_first = P.sliced && P.mode_req == COGDL_BALANCE_AUTO && P.nnz >= (int64_t)P.slice_min * n;
+    if (!P.sliced || mode_first) {
         COGDL_LAUNCH("plan_counts", k_plan_counts<false>, blocks, kPlanBlock, s, rowptr, nullptr, n, P.nnz,
-                     P.group_size, 1, 0, P.row_units, nullptr, nullptr, P.block_sums, keys, n_keys, pad);
+                     P.group_size, 1, 0, nullptr, P.row_units, nullptr, nullptr, P.block_sums, keys, n_keys, pad);
+        const cogdl_status st = totals(0);
+        if (!P.sliced || st != COGDL_OK) return st;
+        n_keys = 0;                               // padded
     }
-    COGDL_LAUNCH("plan_totals", k_plan_totals, 1, kTotalsBlock, s, P.block_sums, (int64_t)blocks, n,
-                 (int)P.mode_req, (int)P.sliced, P.cap_units, P.cap_partials, P.cap_split, P.totals,
-                 P.row_units + n, P.n_parts, P.n_split, P.counters);
-    return COGDL_OK;
+    const int64_t width = ((int64_t)P.n_cols + kSlices - 1) / kSlices;
+    // (a row-split plan asked for by the caller is never sliced)
+    const int32_t slice_min = P.mode_req == COGDL_BALANCE_ROW_SPLIT ? INT32_MAX : P.slice_min;
+    COGDL_LAUNCH("plan_counts", k_plan_counts<true>, blocks, kPlanBlock, s, rowptr, col, n, P.nnz, P.group_size,
+                 width > 0 ? width : 1, slice_min, mode_first ? P.counters + 1 : nullptr, P.row_units, P.alt_units,
+                 P.row_cuts, P.block_sums, keys, n_keys, pad);
+    return totals(1);
 }
 
 // Counts, totals, units in row order, the sort by length, the sorted units: five

@@ -250,3 +250,39 @@ def test_sliced_rebuild_beyond_capacity_falls_back(cg):
             torch.cuda.synchronize()
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("mean", [39, 40, 90])
+def test_long_rows_of_balanced_and_skewed_graphs(cg, mean):
+    """Mean degrees around slice_min (40), from where the mode is found before any row is cut: one
+    plan on a skewed graph, rebuilt on a balanced one of the same size (row split, no row cut) and
+    back, and with the mode asked for."""
+    n, m, nnz, smin, G = 300, 4000, 300 * mean, 40, 16
+    rng = np.random.default_rng(mean)
+    say(f"sliced plan, mean degree {mean}")
+    deg = rng.integers(0, mean // 2, n)
+    long = rng.choice(n, 60, replace=False)
+    deg[long] = 0
+    deg[long] = (nnz - deg.sum()) // 60
+    deg[long[0]] += nnz - deg.sum()
+    graphs = []
+    for d in (deg, np.full(n, mean)):
+        rowptr = np.concatenate([[0], np.cumsum(d)]).astype(np.int32)
+        col = np.concatenate([np.sort(rng.choice(m, k, replace=False)) for k in d]).astype(np.int32)
+        graphs.append((rowptr, col))
+    for mode in ("auto", "neighbor_group", "row_split"):
+        plan = _sliced(cg, dev(graphs[0][0]), dev(graphs[0][1]), nnz, m, (mode, G, smin), 8)
+        try:
+            for rebuilds, g in enumerate((0, 1, 0)):
+                rowptr, col = graphs[g]
+                if rebuilds:
+                    plan.rebuild(dev(rowptr), dev(col))
+                info = plan.info()
+                assert info["mode_name"] == (("neighbor_group", "row_split")[g] if mode == "auto" else mode)
+                got = sorted(map(tuple, plan.units().cpu().numpy()[:, :3].tolist()))
+                sliced = expected_pieces(rowptr, col, m, G, smin, info["mode"] == 2)
+                # (a rebuild whose pieces exceed the sizes taken at creation cuts at group_size only)
+                assert got in (sliced, expected_pieces(rowptr, col, m, G, 1 << 30, info["mode"] == 2))
+                assert g == 1 or got == sliced
+        finally:
+            plan.close()
