@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "cogdl.h"
 
@@ -245,6 +246,14 @@ struct RowGather {
             const uint32_t h = __builtin_amdgcn_raw_buffer_load_b16(rsrc, (int)off, 0, 0);
             o[0] = widen1(h);
         }
+    }
+
+    // The 16 raw bytes at byte offset `off`.
+    __device__ __forceinline__ uint4 load_raw16_off(uint32_t off) const
+    {
+        static_assert(BUF, "buffer gathers only");
+        const auto w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+        return make_uint4(w[0], w[1], w[2], w[3]);
     }
 
     // The 16 raw bytes of elements [idx, idx + VEC) of a 16-byte vector

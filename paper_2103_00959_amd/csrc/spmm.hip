@@ -287,7 +287,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     if (P) set_units(a, tiny ? long_units(*P) : all_units(*P));
     {
         const int64_t upb = wave ? kBlock / kWave : narrow ? kBlock / 8 : kBlock >> m.log2S;
-        SpmmKernel k = wave ? wave_pick(xdt, ydt, m.vec) : pick(m.ch);
+        SpmmKernel k = wave ? wave_pick(xdt, ydt, m.vec, m.S) : pick(m.ch);
         if (!k) return COGDL_ERR_DTYPE;
         int64_t blocks = (units + upb - 1) / upb;
         const bool far = !maxr && (int64_t)F * dtype_bytes(xdt) >= 512 && a.x_bytes > kCachedTable;

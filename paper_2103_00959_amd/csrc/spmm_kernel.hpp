@@ -334,9 +334,14 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm_narrow(SpmmArgs a)
 // Sum of products with a wavefront per unit, for graphs of few units (unit_per_wave): there
 // a call takes as long as its longest unit, a chain of batches of gathers, one memory
 // latency each, so the wavefront's 64 / 2^log2S edge slots (lane = slot * 2^log2S +
-// vector of the row) take the unit's edges side by side, 8 gathers in flight a lane, and
-// their sums are added across lanes at the end.  Rows of one slab and one chunk per lane.
-template <typename TX, typename TY, int VEC>
+// vector of the row) take the unit's edges side by side, up to 8 gathers in flight a lane
+// (as many as the unit still has edges for), and their sums are added across lanes at the
+// end.  Rows of one slab and one chunk per lane.  Short units are bound by the trips to
+// descriptor, indices and rows, so the first two are fetched ahead: 50k rows of 5 edges,
+// 64 / 128 bf16, 31 / 30 us with every trip in turn, 23 / 20 now; 12k rows and 100k edges
+// without a plan, 256 bf16, 66 and 54, 10k and 1M 152 and 125.
+// NARROW: fewer than 8 lanes a row, whose steps of 8 edges a slot can pass the chunk's end.
+template <typename TX, typename TY, int VEC, bool NARROW>
 __global__ __launch_bounds__(kSpmmBlock) void k_spmm_wave(SpmmArgs a)
 {
     constexpr int U = 8;
@@ -353,8 +358,21 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm_wave(SpmmArgs a)
     const uint32_t row_bytes = (uint32_t)a.F * (uint32_t)sizeof(TX);
     const uint32_t lane_off = act ? (uint32_t)fe * (uint32_t)sizeof(TX) : 0u;
     const uint32_t lane_min = act ? 0u : kMaskedOffset;
-    for (int64_t u = walk.first; u < hi; u += walk.step) {
-        const int4 d = fetch_unit(a, u, hi);
+    // (software-pipelined as k_spmm: descriptors a unit ahead, indices a chunk ahead)
+    int64_t u = walk.first;
+    if (u >= hi) return;
+    int4 d = fetch_unit(a, u, hi);
+    uint32_t c_nxt = 0u;
+    float v_nxt = 0.f;
+    const auto fetch_index = [&](int k0, int end) {
+        const int k = k0 + lane < end ? k0 + lane : end - 1;
+        c_nxt = (uint32_t)a.col[k];
+        v_nxt = a.val ? a.val[k] : 1.f;
+    };
+    if (d.z > d.y) fetch_index(d.y, d.z);
+    for (;;) {
+        const int64_t un = u + walk.step;
+        const int4 dn = fetch_unit(a, un, hi);
         const int row = d.x, beg = d.y, end = d.z, part = d.w;
         float acc[VEC];
 #pragma unroll
@@ -362,28 +380,42 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm_wave(SpmmArgs a)
         for (int k0 = beg; k0 < end; k0 += kWave) {
             const int n = (end - k0 < kWave) ? end - k0 : kWave;
             // row offset and weight of edge k0 + lane (past the unit: past the buffer, 0)
-            const bool in = lane < n;
-            const int k = in ? k0 + lane : end - 1;
-            const uint32_t o_cur = in ? (uint32_t)a.col[k] * row_bytes : kMaskedOffset;
-            const float v_cur = in ? (a.val ? a.val[k] : 1.f) : 0.f;
-            for (int j = 0; j < n; j += U * EP) {
-                float xv[U][VEC], vv[U];
+            const uint32_t o_cur = lane < n ? c_nxt * row_bytes : kMaskedOffset;
+            const float v_cur = lane < n ? v_nxt : 0.f;
+            if (k0 + kWave < end) fetch_index(k0 + kWave, end);
+            // UU EP edges from edge j of the chunk on
+            const auto batch = [&](auto uu, int j) {
+                constexpr int UU = decltype(uu)::value;
+                // (16-bit rows stay packed until used: 8 vectors in 32 registers)
+                constexpr bool PACKED = sizeof(TX) == 2 && VEC == 8;
+                float xv[PACKED ? 1 : UU][VEC], vv[UU];
+                uint4 xw[PACKED ? UU : 1];
 #pragma unroll
-                for (int t = 0; t < U; ++t) {
+                for (int t = 0; t < UU; ++t) {
                     const int src = j + t * EP + slot;
-                    const bool inside = src < kWave;               // (fewer than 8 lanes a row)
+                    const bool inside = !NARROW || src < kWave;
                     const uint32_t o = (uint32_t)lane_bcast((int)o_cur, src);
                     const uint32_t off = (inside ? o : kMaskedOffset) + lane_off;
                     const float v = lane_bcast(v_cur, src);
                     vv[t] = inside ? v : 0.f;
-                    X.load_off(off > lane_min ? off : lane_min, xv[t]);
+                    if constexpr (PACKED) xw[t] = X.load_raw16_off(off > lane_min ? off : lane_min);
+                    else X.load_off(off > lane_min ? off : lane_min, xv[t]);
                 }
 #pragma unroll
-                for (int t = 0; t < U; ++t)
+                for (int t = 0; t < UU; ++t) {
+                    float (&x)[VEC] = xv[PACKED ? 0 : t];
+                    if constexpr (PACKED) RowGather<TX, VEC, true>::unpack16(xw[t].x, xw[t].y, xw[t].z, xw[t].w, x);
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vv[t], xv[t][e], acc[e]);
+                    for (int e = 0; e < VEC; ++e) acc[e] = fmaf(vv[t], x[e], acc[e]);
+                }
+            };
+            for (int j = 0; j < n; j += U * EP) {
+                if (n - j > 4 * EP) batch(std::integral_constant<int, 8>{}, j);
+                else if (n - j > 2 * EP) batch(std::integral_constant<int, 4>{}, j);
+                else batch(std::integral_constant<int, 2>{}, j);
             }
         }
+        if (dn.z > dn.y) fetch_index(dn.y, dn.z);
         for (int off = LQ; off < kWave; off <<= 1)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc[e] += lane_xor(acc[e], off);
@@ -400,25 +432,34 @@ __global__ __launch_bounds__(kSpmmBlock) void k_spmm_wave(SpmmArgs a)
                 store_vec<float, VEC>(a.partials, (int64_t)part * a.pstride + fe, acc);
             }
         }
+        if (un >= hi) break;
+        u = un;
+        d = dn;
     }
 }
 
 using SpmmKernel = void (*)(SpmmArgs);
 
-template <typename TX>
-SpmmKernel wave_pick_y(int ydt, int vec)
+template <typename TX, typename TY>
+SpmmKernel wave_pick_v(int vec, bool narrow)
 {
     constexpr int V = (int)(16 / sizeof(TX));
-    if (ydt == COGDL_F32) return vec == 1 ? k_spmm_wave<TX, float, 1> : k_spmm_wave<TX, float, V>;
-    if (ydt == COGDL_BF16) return vec == 1 ? k_spmm_wave<TX, bf16_t, 1> : k_spmm_wave<TX, bf16_t, V>;
-    return vec == 1 ? k_spmm_wave<TX, f16_t, 1> : k_spmm_wave<TX, f16_t, V>;
+    if (vec == 1) return narrow ? k_spmm_wave<TX, TY, 1, true> : k_spmm_wave<TX, TY, 1, false>;
+    return narrow ? k_spmm_wave<TX, TY, V, true> : k_spmm_wave<TX, TY, V, false>;
 }
 
-inline SpmmKernel wave_pick(int xdt, int ydt, int vec)
+// S: lanes a row (at most 32).
+inline SpmmKernel wave_pick(int xdt, int ydt, int vec, int S)
 {
-    if (xdt == COGDL_F32) return wave_pick_y<float>(ydt, vec);
-    if (xdt == COGDL_BF16) return wave_pick_y<bf16_t>(ydt, vec);
-    return wave_pick_y<f16_t>(ydt, vec);
+    const auto pick_y = [&](auto tx) -> SpmmKernel {
+        using TX = decltype(tx);
+        if (ydt == COGDL_F32) return wave_pick_v<TX, float>(vec, S < 8);
+        if (ydt == COGDL_BF16) return wave_pick_v<TX, bf16_t>(vec, S < 8);
+        return wave_pick_v<TX, f16_t>(vec, S < 8);
+    };
+    if (xdt == COGDL_F32) return pick_y(float{});
+    if (xdt == COGDL_BF16) return pick_y(bf16_t{});
+    return pick_y(f16_t{});
 }
 
 template <typename TX, typename TY>
