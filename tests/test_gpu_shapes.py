@@ -336,3 +336,24 @@ def test_linear_grids(cg, n, k, m):
         rows = x[r0:r0 + 4096].double()
         bound = rows.abs() @ w.double().abs().T * (k * 2.0 ** -24)   # fp32 sums of exact products
         assert torch.all((y[r0:r0 + 4096].double() - rows @ w.double().T).abs() <= bound), (n, k, m, r0)
+
+
+@pytest.mark.parametrize("n", [39000, 42000])
+@pytest.mark.parametrize("mode", ["auto", "neighbor_group", "row_split"])
+@pytest.mark.parametrize("F,xk", [(41, "bf16"), (64, "bf16"), (33, "f32")])
+def test_spmm_small_groups(cg, n, mode, F, xk):
+    """Plans cut into groups of 32 edges around the size (2^18 edges) from where their units stop
+    running a wavefront each, with the mode asked for and chosen."""
+    import torch
+    g = _graph(F, n=n, m=3000)
+    assert (g.nnz > 1 << 18) == (n == 42000)
+    say(f"spmm groups of 32 n={n} {mode} F={F} {xk}")
+    rp, cl, vl = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, F), 17 + F, xk)
+    Yr, Ar = oracle.spmm(g.rowptr, g.col, g.val, xh, x_dtype=xc)
+    plan = cg.Plan(rp, g.nnz, max_feat=F, mode=mode, group_size=32)
+    try:
+        Y = cg.spmm(rp, cl, vl, xd, plan=plan, out_dtype=torch.float32)
+        assert scaled_error(Y, Yr, Ar) <= tol_for("f32"), (n, mode, F, xk)
+    finally:
+        plan.close()
