@@ -50,6 +50,33 @@ bool unit_per_wave(const Plan *plan, int S, int64_t units, int64_t nnz)
     return !plan && nnz >= units * (256 / S);
 }
 
+// Whether rows of no whole number of vectors run one element per lane.  Vectors need fewer
+// loads, but a call that takes as long as its longest unit wants that chain short, and 64
+// element lanes take 16 edges a step where vectors on 8 or 16 lanes take 8 (max and add,
+// with more arithmetic a feature, also spend longer in a step).  Without a plan a hub row
+// is such a chain on any skewed graph; with one, the groups are on small graphs.  A plan
+// asked for by rows is for even rows.  us, elements / vectors, skewed graphs:
+//   no plan, sums: 100k rows and 500k edges, 41 fp32 211 / 351, 100 bf16 298 / 325; 170k and
+//     2.5M 606 / 906, 913 / 1151 (but 50k even rows of 5: 25 / 13, 22 / 13);
+//   no plan, max: 24k and 600k, 41 fp32 326 / 641, 100 bf16 513 / 886 (40k even rows of 25:
+//     37 / 25, 53 / 36);
+//   plan, max: 3k and 15k, 41 bf16 26 / 60, 100 bf16 31 / 58; 24k and 600k 38 / 71, 51 / 75;
+//     10k and 1M 42 / 65, 51 / 66, but 40k even rows of 25 41 / 24, 54 / 39; 170k and 2.5M
+//     104 / 107, 173 / 128;
+//   plan, add: 24k and 600k, 41 bf16 28 / 47, 41 fp32 28 / 35; 10k and 1M 36 / 45, 34 / 27;
+//   plan, sums: 100k and 500k, 41 fp32 35 / 42, 41 bf16 69 / 112 (both directions), 50k and
+//     500k 60 / 79; 100k and 2M 130 / 130, 24k and 200k 48 / 45.
+bool element_lanes(const Plan *plan, const RowMap &m, bool sums, int64_t units, int64_t nnz, int64_t rows,
+                   bool wave)
+{
+    const bool groups = plan && plan->mode_req != COGDL_BALANCE_ROW_SPLIT;
+    if (!sums) return m.S <= 16 && (!plan || (groups && nnz < 3 << 18));
+    if (wave && !(plan && m.S == 8 && units > 32768)) return false;
+    if (!plan) return m.S <= 16;
+    return units > 32768 && units <= 131072 && nnz < 16 * rows &&
+           (m.S == 8 || (groups && m.S == 16 && m.vec == 4 && plan->group_size >= kWave));
+}
+
 // Y[row, :] = sum of the row's partial rows (times 1 / degree for mean).  A
 // wavefront per split row (grid-stride over the device-side count, uniform
 // per wavefront), VEC features per lane: slot g goes to chain g mod 4, the
@@ -244,14 +271,8 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     const int64_t units = P ? P->cap_units : out_rows;
     const bool sums = !maxr && compute != COGDL_COMPUTE_ADD && compute != COGDL_COMPUTE_SUB;
     const bool offsets = sums && (uint64_t)in_rows * (uint64_t)F * (uint64_t)dtype_bytes(xdt) <= kMaskedOffset;
-    // Ragged rows of 33 to 64 elements on 8 lanes make longer chains than on 64 element
-    // lanes (8 edges a step against 16): without a plan, and on graphs of middle size
-    // with short rows, they keep those (41 bf16, us, elements / vectors: 100k rows and
-    // 500k edges 69 / 112, 50k and 500k 60 / 79, 169k without a plan 1227 / 2627; but 100k
-    // and 2M 130 / 130, 24k and 200k 48 / 45).
-    if (m.vec > 1 && m.S == 8 && F % m.vec != 0 && !(offsets && unit_per_wave(P, m.S, units, nnz) &&
-                                                     (units <= 32768 || !P)) &&
-        (!P || (units > 32768 && units <= 131072 && nnz < 16 * (int64_t)out_rows)))
+    if (m.vec > 1 && F % m.vec != 0 &&
+        element_lanes(P, m, sums, units, nnz, out_rows, offsets && m.ch == 1 && unit_per_wave(P, m.S, units, nnz)))
         m = element_map(F);
     SpmmArgs a;
     a.units = P ? P->units : nullptr;

@@ -357,3 +357,32 @@ def test_spmm_small_groups(cg, n, mode, F, xk):
         assert scaled_error(Y, Yr, Ar) <= tol_for("f32"), (n, mode, F, xk)
     finally:
         plan.close()
+
+
+@pytest.mark.parametrize("n", [118000, 124000])
+@pytest.mark.parametrize("F,xk", [(33, "bf16"), (65, "bf16"), (127, "f16"), (33, "f32"), (63, "f32")])
+def test_ragged_rows_past_the_element_lanes(cg, n, F, xk):
+    """Max (with its edge ids), add and the sums at widths of no whole vector around the size
+    (3 2^18 edges) from where max and add of a plan stop running an element per lane."""
+    import torch
+    g = _graph(F, n=n, m=3000)
+    assert (g.nnz >= 3 << 18) == (n == 124000)
+    say(f"max and add n={n} F={F} {xk}")
+    rp, cl, vl = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, F), 5 + F, xk)
+    Mr, _, Er = oracle.gspmm(g.rowptr, g.col, g.val, xh, "max", x_dtype=xc)
+    Sr, Ar, _ = oracle.gspmm(g.rowptr, g.col, g.val, xh, "sum", compute="add", x_dtype=xc)
+    Yr, Yar = oracle.spmm(g.rowptr, g.col, g.val, xh, x_dtype=xc)
+    for kw in (None, {}, {"mode": "row_split"}, {"mode": "neighbor_group", "group_size": 40}):
+        plan = None if kw is None else cg.Plan(rp, g.nnz, max_feat=F, **kw)
+        try:
+            top, arg = cg.gspmm(rp, cl, vl, xd, "max", plan=plan, out_dtype=torch.float32, return_arg=True)
+            assert np.array_equal(to_f64(top), oracle.decode(oracle.round_to(Mr, oracle.F32), oracle.F32).reshape(Mr.shape))
+            assert np.array_equal(arg.cpu().numpy(), Er)
+            add = cg.gspmm(rp, cl, vl, xd, "sum", compute="add", plan=plan, out_dtype=torch.float32)
+            assert scaled_error(add, Sr, Ar) <= TOL_F32, (n, F, xk, kw)
+            Y = cg.spmm(rp, cl, vl, xd, plan=plan, out_dtype=torch.float32)
+            assert scaled_error(Y, Yr, Yar) <= TOL_F32, (n, F, xk, kw)
+        finally:
+            if plan is not None:
+                plan.close()
