@@ -315,7 +315,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
         SpmmKernel k = wave ? wave_pick(xdt, ydt, m.vec, m.S) : pick(m.ch);
         if (!k) return COGDL_ERR_DTYPE;
         int64_t blocks = (units + upb - 1) / upb;
-        const bool far = !maxr && (int64_t)F * dtype_bytes(xdt) >= 512 && a.x_bytes > kCachedTable;
+        const bool far = P && !maxr && (int64_t)F * dtype_bytes(xdt) >= 512 && a.x_bytes > kCachedTable;
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock, 0, far ? kFarTableBlocks : 0);
         if (blocks > res) blocks = res;
         blocks = list_grid(blocks, a.lists);
