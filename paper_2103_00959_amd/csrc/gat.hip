@@ -696,7 +696,7 @@ cogdl_status gat_aggregate_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, con
     if (n_rows == 0) return COGDL_OK;
 
     const bool aligned = ((uintptr_t)X % 16 == 0) && ((uintptr_t)Y % 16 == 0);
-    const HeadMap m = head_map(H, D, dtype_bytes(x_dtype));
+    const HeadMap m = head_map(H, D, dtype_bytes(x_dtype), soft);
     // projected source scores: each head a power of two of whole aligned vectors, up to
     // one wavefront of them
     const int v16 = 16 / dtype_bytes(x_dtype), hl = D / v16;

@@ -812,7 +812,7 @@ cogdl_status gat_backward_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, cons
     if (n_cols == 0) return COGDL_OK;
 
     // pass 2 on the CSC: dX and ds_src
-    const HeadMap m = head_map(H, D, dtype_bytes(dy_dtype));
+    const HeadMap m = head_map(H, D, dtype_bytes(dy_dtype), true);
     GatArgs g{};
     g.units = Pc ? Pc->units : nullptr;
     g.n_rows = n_cols;

@@ -406,7 +406,7 @@ RowMap span_map(int64_t width, int elem_bytes)
 
 RowMap element_map(int64_t width) { return lane_map(width, 1); }
 
-HeadMap head_map(int H, int D, int elem_bytes)
+HeadMap head_map(int H, int D, int elem_bytes, bool share)
 {
     HeadMap m;
     const int v16 = 16 / elem_bytes;
@@ -419,9 +419,9 @@ HeadMap head_map(int H, int D, int elem_bytes)
         const int heads = next_pow2(H);
         int L = next_pow2(vecs);
         while (L * heads < 8) L *= 2;
-        if (L * heads <= fit) m.L = L;
+        if (share && L * heads <= fit) m.L = L;
         m.S = fit;
-        if ((m.L & (m.L - 1)) == 0) m.lm = log2i(m.L < 8 ? m.L : 8);
+        if (share && (m.L & (m.L - 1)) == 0) m.lm = log2i(m.L < 8 ? m.L : 8);
     } else {
         const int64_t ch = (slots + kWave - 1) / kWave;
         m.S = kWave;
@@ -429,7 +429,7 @@ HeadMap head_map(int H, int D, int elem_bytes)
         m.n_slabs = (int)((slots + (int64_t)m.S * m.ch - 1) / ((int64_t)m.S * m.ch));
     }
     m.log2S = log2i(m.S);
-    m.tiny = m.ch == 1 && m.S / 4 >= H && (m.S >= 16 || m.lm == 0);
+    m.tiny = m.ch == 1 && m.S >= 16 && m.S / 4 >= H;
     return m;
 }
 

@@ -386,3 +386,12 @@ def test_ragged_rows_past_the_element_lanes(cg, n, F, xk):
         finally:
             if plan is not None:
                 plan.close()
+
+
+@pytest.mark.parametrize("H,D,xk", [(3, 35, "bf16"), (3, 40, "bf16"), (3, 18, "f32"), (5, 20, "bf16"), (16, 3, "f32"),
+                                    (12, 3, "bf16"), (6, 10, "f32")])
+def test_head_maps_of_odd_lane_counts(cg, H, D, xk):
+    """Heads of vectors on a lane count that is no power of two, and heads whose lanes are padded to
+    one where scores are shared but not on given weights."""
+    test_head_maps_forward(cg, H, D, xk)
+    test_head_maps_backward(cg, H, D, xk)
