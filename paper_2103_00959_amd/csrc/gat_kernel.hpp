@@ -322,9 +322,12 @@ void k_gat(GatArgs a)
                 // the multi-chunk (tiny-unit) kernels keep 16-bit rows packed, one
                 // 16-byte word per chunk, and widen them where used: the projected ones
                 // with a_src in LDS and the given-score four-chunk one gain a wavefront
-                // per SIMD (the other kernels gain none)
+                // per SIMD; the ones that share given scores spill without it (68 bytes a
+                // lane on 2 lanes: 1M edges 4 x 16 bf16 28 us, 24 packed, 8M 302 and 284).
+                // The other kernels gain none, the backward's sharing one loses 5%.
                 constexpr bool XPACK = (ASRC_LDS && sizeof(TX) == 2 && VEC == 8) ||
-                                       gat_given_packed<VEC, CH, BUF, BWD, PM, (int)sizeof(TX)>;
+                                       gat_given_packed<VEC, CH, BUF, BWD, PM, (int)sizeof(TX)> ||
+                                       (DIST && !BWD && !PROJ && sizeof(TX) == 2 && VEC == 8);
                 float xv[XPACK ? 1 : U][XPACK ? 1 : CH][XPACK ? 1 : VEC];
                 uint4 xw[XPACK ? U : 1][XPACK ? CH : 1];
 #pragma unroll
@@ -415,9 +418,17 @@ void k_gat(GatArgs a)
                     float wt[U];
                     share_weights<LM>(own, wt);
 #pragma unroll
-                    for (int t = 0; t < U; ++t)
+                    for (int t = 0; t < U; ++t) {
+                        float xe[VEC];
+                        if constexpr (XPACK) {
+                            RowGather<TX, VEC, BUF>::unpack16(xw[t][0].x, xw[t][0].y, xw[t][0].z, xw[t][0].w, xe);
+                        } else {
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) acc[0][e] = fmaf(wt[t], xv[t][0][e], acc[0][e]);
+                            for (int e = 0; e < VEC; ++e) xe[e] = xv[t][0][e];
+                        }
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) acc[0][e] = fmaf(wt[t], xe[e], acc[0][e]);
+                    }
                     continue;
                 }
                 if constexpr (ASRC_LDS) {
