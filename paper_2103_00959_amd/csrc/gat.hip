@@ -737,7 +737,8 @@ cogdl_status gat_aggregate_impl(int32_t n_rows, int32_t n_cols, int64_t nnz, con
         GatKernel k = proj ? gat_pick_proj(x_dtype, y_dtype, m.ch, buf, m.lm)
                            : gat_pick<false>(x_dtype, y_dtype, m.vec, m.ch, buf, soft ? m.lm : 0);
         int64_t blocks = (units + upb - 1) / upb;
-        const bool far = P && soft && !proj && m.lm > 0 && a.x_bytes > kCachedTable;
+        const bool far = P && soft && a.x_bytes > kCachedTable &&
+                         (proj ? m.lm == 3 && W * dtype_bytes(x_dtype) >= 512 : m.lm > 0);
         const int64_t res = resident_blocks(reinterpret_cast<const void *>(k), kBlock, 0, far ? kFarTableBlocks : 0);
         if (blocks > res) blocks = res;
         blocks = list_grid(blocks, a.lists);

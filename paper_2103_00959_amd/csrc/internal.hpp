@@ -138,10 +138,13 @@ int resident_blocks(const void *kernel, int block, size_t shm = 0, int most = 0)
 // fp32 rows of 512 bytes 0.96 and 0.94; rows of 256 bytes 1.27 and 1.32, so not there).
 // Aggregation on given scores with a sliced plan, 122M edges: 4 x 64 bf16 7.68 and 7.44,
 // 4 x 32 bf16 4.35 and 4.22, 8 x 16 fp32 7.40 and 7.30; with a plain one 9.33 and 9.33 (of a
-// training step's forward and backward, 26 ms at 4 x 64, that is within the noise).  Tables
-// the caches hold want every wavefront, and so do calls without a plan, which wait for their
-// longest row: sums on 600k rows and 3M edges of 256 fp32 1.18 and 1.31, 2.4M and 12M 3.91
-// and 4.26, the aggregation on 1.2M and 6M at 4 x 64 bf16 2.69 and 2.90.
+// training step's forward and backward, 26 ms at 4 x 64, that is within the noise); on
+// projected scores, rows of 512 bytes and more on 8 lanes or more a head: 4 x 64 bf16 plain
+// 7.62 and 7.37, 8 x 64 17.0 and 16.5 (1 x 128, 256 bytes, 3.22 and 3.41; 4 x 32, 4 lanes a
+// head, sliced, 2.64 and 2.86).  Tables the caches hold want every wavefront, and so do
+// calls without a plan, which wait for their longest row: sums on 600k rows and 3M edges
+// of 256 fp32 1.18 and 1.31, 2.4M and 12M 3.91 and 4.26, the aggregation on 1.2M and 6M
+// at 4 x 64 bf16 2.69 and 2.90.
 constexpr uint64_t kCachedTable = 256ull << 20;
 constexpr int kFarTableBlocks = 3;
 
