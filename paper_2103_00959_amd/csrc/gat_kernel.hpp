@@ -167,6 +167,15 @@ __device__ __forceinline__ void share_weights(const float (&own)[8 >> LM], float
     if constexpr (T < 7) share_weights<LM, T + 1>(own, w);
 }
 
+constexpr float kLog2eF = 1.44269504f;
+
+// m log2 e of a running maximum, 0 while every score so far is -inf: those edges (sources
+// masked out by their score) then weigh 2^-inf = 0 instead of NaN, however many of them
+// open a unit and however long its batches are.  A row of such edges only ends NaN, as
+// its softmax is.  (Projected scores are -inf only for infinite features, whose sum is
+// NaN anyway; there the extra step in the chain would cost hub rows 5%.)
+__device__ __forceinline__ float max_log2(float m) { return m > -INFINITY ? m * kLog2eF : 0.f; }
+
 // PM (source-score mode): 0 and 3 read s_src (or, BWD / alpha_in, the given
 // weights); 1 and 2 form it from the gathered row.
 // PM = 1: the source score of each edge is formed from the gathered
@@ -241,7 +250,6 @@ void k_gat(GatArgs a)
     const RowGather<TX, VEC, BUF> X(a.X, a.x_bytes);
     const int32_t *__restrict__ col = a.col;
     const float *__restrict__ wsrc = soft ? a.s_src : a.alpha_in;
-    constexpr float kLog2eF = 1.44269504f;
     // PROJ: this lane's VEC entries of a_src, and the lanes per head.  With
     // several chunks per lane (the tiny-unit kernels) the slab's a_src sits in
     // LDS instead and is read per batch, which keeps CH * VEC registers free.
@@ -408,7 +416,7 @@ void k_gat(GatArgs a)
                             for (int e = 0; e < VEC; ++e) acc[0][e] *= r;
                             m[0] = mb;
                         }
-                        const float ml = m[0] * kLog2eF;
+                        const float ml = PROJ ? m[0] * kLog2eF : max_log2(m[0]);
 #pragma unroll
                         for (int r = 0; r < EPL; ++r) {
                             own[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], kLog2eF, -ml));
@@ -496,10 +504,8 @@ void k_gat(GatArgs a)
                             m[c] = mb;
                         }
                         // exp(w - m) = 2^(w log2 e - m log2 e): one fma per edge; a masked
-                        // edge (-inf) gives 2^-inf = 0.  m is finite here on every lane that
-                        // stores (its first batch holds a valid edge); a lane past the row's
-                        // width (no store) may compute NaN, which no other lane reads.
-                        const float ml = m[c] * kLog2eF;
+                        // edge (-inf) gives 2^-inf = 0.
+                        const float ml = PROJ ? m[c] * kLog2eF : max_log2(m[c]);
                         float zb = 0.f;
 #pragma unroll
                         for (int t = 0; t < U; ++t) {
@@ -569,7 +575,7 @@ void k_gat(GatArgs a)
             float rz[CH];
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                rz[c] = (soft && z[c] > 0.f) ? 1.f / z[c] : 1.f;
+                rz[c] = (soft && end > beg) ? 1.f / z[c] : 1.f;
                 // the row's softmax state, from which alpha = alpha_value(e, m, 1/z) can be
                 // rebuilt (every lane of the head holds it; the lane of its first feature writes)
                 if (soft && a.row_stats != nullptr && first[c]) {

@@ -395,3 +395,34 @@ def test_head_maps_of_odd_lane_counts(cg, H, D, xk):
     one where scores are shared but not on given weights."""
     test_head_maps_forward(cg, H, D, xk)
     test_head_maps_backward(cg, H, D, xk)
+
+
+@pytest.mark.parametrize("H,D,xk", [(1, 41, "bf16"), (1, 5, "f32"), (2, 3, "bf16"), (4, 16, "bf16"), (8, 16, "f32"),
+                                    (8, 8, "bf16"), (3, 35, "bf16"), (4, 64, "bf16"), (8, 51, "f32")])
+def test_masked_sources_open_a_row(cg, H, D, xk):
+    """Sources masked out by a score of -inf weigh nothing, however many of them open a row or a
+    group: rows of 1 to 40 edges whose first edges but one, two or five are masked."""
+    import torch
+    m = 64
+    deg = np.repeat(np.arange(1, 41), 3)
+    keep = np.minimum(np.tile([1, 2, 5], 40), deg)
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    col = np.concatenate([np.concatenate([np.arange(d - k), 40 + np.arange(k)]) for d, k in zip(deg, keep)]).astype(np.int32)
+    g = synth.Graph(rowptr, col, None, deg.size, m)
+    say(f"masked sources H={H} D={D} {xk}")
+    rng = np.random.default_rng(H * D)
+    sd, ss = rng.standard_normal((g.n_rows, H)).astype(np.float32), rng.standard_normal((m, H)).astype(np.float32)
+    ss[:40] = -np.inf
+    xh, xc, xd = features((m, H, D), 60 + D, xk)
+    Yr, Ar = oracle.gat(rowptr, col, sd, ss, xh.reshape(m, H * D), H, D, slope=0.2, x_dtype=xc)
+    rp, cl = dev(rowptr), dev(col)
+    for plan in _plans(cg, rp, cl, g, H * D, H):
+        Y = cg.gat_aggregate(rp, cl, dev(sd), dev(ss), xd, 0.2, plan=plan, out_dtype=torch.float32)
+        assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= TOL_F32, (H, D, xk)
+    for G in (3, 16):
+        plan = cg.Plan(rp, g.nnz, max_feat=H * D, max_heads=H, mode="neighbor_group", group_size=G)
+        try:
+            Y = cg.gat_aggregate(rp, cl, dev(sd), dev(ss), xd, 0.2, plan=plan, out_dtype=torch.float32)
+            assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= TOL_F32, (H, D, xk, G)
+        finally:
+            plan.close()
