@@ -653,7 +653,13 @@ cogdl_status rows_pass(BwdArgs a, const Plan *P, int xdt, int pdt, const char *n
     const int pk = a.row_stats ? kParkStats : (a.dalpha && a.dscore) ? kParkSep : kParkPair;
     const int vec = a.D >= v16 ? v16 : 1;
     int L = next_pow2((a.D + vec - 1) / vec);
-    if (xdt == pdt && L <= kWave) {
+    // Dot products alone of up to 4 short ragged heads: the general kernel takes 64 / H edges
+    // side by side, the feature-parallel one 8, and a lane sums up to 8 features faster than
+    // a long row's chain of batches goes on (2 heads of 5 bf16, us, general / parallel:
+    // without a plan 600k edges 98 / 469, 2.5M 378 / 1183, but 8M in rows of 16 238 / 124; with
+    // one 15k 13 / 27, 600k 18 / 30, 2.5M 94 / 51; 8 heads of 6 without a plan 456 / 476).
+    const bool short_heads = DOT && a.D <= 8 && a.H <= 4 && (a.D & (a.D - 1)) != 0 && (!P || P->nnz < 3 << 18);
+    if (xdt == pdt && L <= kWave && !short_heads) {
         // sub-groups of at least 8 lanes, so that a chunk of column indices (one per lane)
         // fills a batch of 8 edges
         const int hp = next_pow2(a.H);

@@ -426,3 +426,29 @@ def test_masked_sources_open_a_row(cg, H, D, xk):
             assert scaled_error(Y.reshape(Yr.shape), Yr, Ar) <= TOL_F32, (H, D, xk, G)
         finally:
             plan.close()
+
+
+@pytest.mark.parametrize("n", [118000, 124000])
+@pytest.mark.parametrize("H,D,xk", [(1, 3, "bf16"), (2, 5, "f32"), (4, 7, "bf16"), (5, 7, "f16"), (2, 9, "f32")])
+def test_dots_of_short_heads(cg, n, H, D, xk):
+    """Dot products of short ragged heads around the size (3 2^18 edges) from where a plan's run
+    the feature-parallel kernel, and heads of one too many or one too wide for the other."""
+    import torch
+    g = _graph(D, n=n, m=3000)
+    assert (g.nnz >= 3 << 18) == (n == 124000)
+    say(f"dot n={n} H={H} D={D} {xk}")
+    rp, cl, _ = graph_to_dev(g)
+    xh, xc, xd = features((g.n_cols, H, D), 70 + D, xk)
+    ph, pc, pd = features((g.n_rows, H, D), 71 + D, xk)
+    ref, ab = oracle.sddmm_dot(g.rowptr, g.col, ph.reshape(g.n_rows, H * D), xh.reshape(g.n_cols, H * D), H, D,
+                               p_dtype=pc, q_dtype=xc)
+    for kw in (None, {}, {"mode": "neighbor_group", "group_size": 40}):
+        plan = None if kw is None else cg.Plan(rp, g.nnz, max_feat=H * D, max_heads=H, **kw)
+        try:
+            out, buf = _guarded((g.nnz, H), torch.float32, 0)
+            cg.sddmm_dot(rp, cl, pd, xd, plan=plan, out=out)
+            assert scaled_error(out, ref, ab) <= TOL_F32, (n, H, D, xk, kw)
+            _untouched(buf, g.nnz * H, 0)
+        finally:
+            if plan is not None:
+                plan.close()
