@@ -227,8 +227,11 @@ __global__ __launch_bounds__(kBlock) void k_bwd_rows(BwdArgs a)
         const int4 dn = fetch_bwd_unit(a, un, hi);
         const int row = d.x, beg = d.y, end = d.z, part = d.w;
         // a whole row whose parked values fit this sub-group's LDS share parks them there
+        // (pairs of heads on one lane, 8 edges of which a lane parks in a batch, in the records:
+        // 8 heads of 8 bf16, 2.5M edges, 453 us through LDS, 415)
+        constexpr bool PARK_LDS = !DOT && !(LM == 0 && PK != kParkSep);
         float *const lds =
-            (!DOT && part < 0 && (end - beg) * a.HG * (PK == kParkSep ? 1 : 2) <= a.park_cap) ? park_mine : nullptr;
+            (PARK_LDS && part < 0 && (end - beg) * a.HG * (PK == kParkSep ? 1 : 2) <= a.park_cap) ? park_mine : nullptr;
         float p[PACKED ? 1 : VEC];
         uint4 pw = make_uint4(0u, 0u, 0u, 0u);
         if constexpr (VEC == 1) {
