@@ -191,10 +191,15 @@ __device__ __forceinline__ void store_out(T *__restrict__ p, int64_t i, const fl
 constexpr int kBufferWord3 = 0x00020000;
 // Largest buffer the 32-bit offsets of the buffer gathers address.
 constexpr uint64_t kBufferMaxBytes = 0xffffff00ull;
-// The same for gathers whose masked offset (kMaskedOffset, past every such buffer) is
-// still added to a lane's offset inside a row of at most four 16-byte vectors: the sum
-// stays past the buffer and below 2^32.
-constexpr uint32_t kMaskedOffset = 0xfff00000u;
+// The sums that form row offsets ahead (k_spmm_narrow, k_spmm_wave) add a lane's offset in
+// its row to a masked edge's offset too.  Their tables have at most kOffsetTableBytes bytes
+// (the host checks; not kBufferMaxBytes), the masked offset lies at that size, and a lane's
+// offset, below kMaskedSpan, keeps the sum past the table and below 2^32.
+constexpr uint64_t kOffsetTableBytes = 0xfff00000ull;
+constexpr uint64_t kMaskedSpan = 1ull << 20;
+constexpr uint32_t kMaskedOffset = (uint32_t)kOffsetTableBytes;
+static_assert(kOffsetTableBytes + kMaskedSpan <= (1ull << 32), "masked offsets do not wrap");
+static_assert(kWave * 16 <= kMaskedSpan, "a row of one 16-byte vector a lane");
 
 template <typename T, int VEC> struct VecBytes { static constexpr int value = (int)sizeof(T) * VEC; };
 

@@ -270,7 +270,7 @@ cogdl_status spmm_common(int32_t out_rows, int32_t in_rows, int64_t nnz, const i
     RowMap m = span_map(F, dtype_bytes(xdt));
     const int64_t units = P ? P->cap_units : out_rows;
     const bool sums = !maxr && compute != COGDL_COMPUTE_ADD && compute != COGDL_COMPUTE_SUB;
-    const bool offsets = sums && (uint64_t)in_rows * (uint64_t)F * (uint64_t)dtype_bytes(xdt) <= kMaskedOffset;
+    const bool offsets = sums && (uint64_t)in_rows * (uint64_t)F * (uint64_t)dtype_bytes(xdt) <= kOffsetTableBytes;
     if (m.vec > 1 && F % m.vec != 0 &&
         element_lanes(P, m, sums, units, nnz, out_rows, offsets && m.ch == 1 && unit_per_wave(P, m.S, units, nnz)))
         m = element_map(F);
