@@ -185,16 +185,6 @@ cogdl_status check_codec(int64_t n, int32_t F, int32_t bits, int32_t group)
     return COGDL_OK;
 }
 
-// Workgroups for `waves` wavefronts of work, at most what fits on the chip at once.
-unsigned resident_grid(const void *kernel, int64_t waves)
-{
-    int64_t b = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
-    const int64_t res = resident_blocks(kernel, kBlock);
-    if (b > res) b = res;
-    if (b < 1) b = 1;
-    return (unsigned)b;
-}
-
 unsigned codec_grid(int64_t groups)
 {
     int64_t b = (groups + (kBlock / kWave) - 1) / (kBlock / kWave);

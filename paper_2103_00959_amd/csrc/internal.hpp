@@ -44,7 +44,6 @@ struct Plan {
     uint32_t *block_sums = nullptr; // 8 sums of each workgroup of the count pass
     int32_t *counters = nullptr;  // [8]: 0 close-degree rows, 1 chosen mode,
                                   //      2 units longer than kTinyUnit, 3 zero,
-                                  //      4 sliced plan: 1 when its rows were sliced,
                                   //      5 1 when the last build's totals exceeded the
                                   //        capacities (the plan was left empty)
                                   //      6 which row counts the build used
@@ -213,8 +212,9 @@ inline int log2i(int v)
     return l;
 }
 
-// Launch geometry of the SpMM gather kernels for one row of `width` elements: VEC elements per lane, S lanes per edge row, CH chunks
-// per lane and the number of feature slabs.
+// Launch geometry of the SpMM gather kernels for one row of `width` elements: VEC
+// elements per lane, S lanes per edge row, CH chunks per lane and the number of feature
+// slabs.
 struct RowMap {
     int vec = 1;
     int S = 64;

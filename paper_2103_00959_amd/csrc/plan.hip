@@ -82,8 +82,8 @@ template <bool SLICED>
 __global__ __launch_bounds__(kPlanBlock) void k_plan_counts(
     const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int32_t n_rows, int64_t nnz, int32_t G,
     int64_t width, int32_t slice_min, const int32_t *__restrict__ mode, int32_t *__restrict__ row_units,
-    int32_t *__restrict__ alt_units, int32_t *__restrict__ row_cuts, uint32_t *__restrict__ sums, uint32_t *__restrict__ keys, int64_t n_keys,
-    uint32_t pad)
+    int32_t *__restrict__ alt_units, int32_t *__restrict__ row_cuts, uint32_t *__restrict__ sums,
+    uint32_t *__restrict__ keys, int64_t n_keys, uint32_t pad)
 {
     for (int64_t k = (int64_t)blockIdx.x * kPlanBlock + threadIdx.x; k < n_keys; k += (int64_t)gridDim.x * kPlanBlock)
         keys[k] = pad;
@@ -204,7 +204,6 @@ __global__ __launch_bounds__(kTotalsBlock) void k_plan_totals(uint32_t *__restri
         counters[1] = mode;
         counters[2] = 0;
         counters[3] = 0;
-        counters[4] = sliced && set != 1 ? 1 : 0;
         counters[5] = ok ? 0 : 1;
         counters[6] = set;
         set_sh = ok ? set : -1;

@@ -58,10 +58,10 @@ __global__ __launch_bounds__(WAVES * kWave) void k_digit_scan(int32_t *__restric
 
 // Per-tile histogram of one digit (bits [shift, shift + dbits) of the key),
 // stored digit-major, so that the sums over a digit's tiles (k_digit_scan) and over the
-// digits before it (the scatter) give every (digit, tile) start slot.  Each wavefront counts into kHistCopies LDS copies
-// (lane % kHistCopies picks one), so the lanes of a wavefront that share a
-// digit, common on the high digits of power-law keys, collide on one LDS
-// address a quarter as often.
+// digits before it (the scatter) give every (digit, tile) start slot.  Each wavefront
+// counts into kHistCopies LDS copies (lane % kHistCopies picks one), so the lanes of a
+// wavefront that share a digit, common on the high digits of power-law keys, collide on
+// one LDS address a quarter as often.
 constexpr int kHistCopies = 4;
 
 __global__ __launch_bounds__(kSortBlock) void k_radix_hist(const uint32_t *__restrict__ keys, int64_t n,
