@@ -60,8 +60,8 @@ def _untouched(buf, n, by):
 
 def _plans(cg, rp, cl, g, width, heads=0):
     yield None
-    for kw in ({"mode": "neighbor_group", "group_size": 40}, {"mode": "neighbor_group", "group_size": 64}, {"mode": "neighbor_group", "group_size": 40, "col": cl,
-                                                              "n_cols": g.n_cols, "slice_min": 30}):
+    for kw in ({"mode": "neighbor_group", "group_size": 40}, {"mode": "neighbor_group", "group_size": 64},
+               {"mode": "neighbor_group", "group_size": 40, "col": cl, "n_cols": g.n_cols, "slice_min": 30}):
         p = cg.Plan(rp, g.nnz, max_feat=width, max_heads=heads, **kw)
         try:
             yield p
@@ -452,3 +452,125 @@ def test_dots_of_short_heads(cg, n, H, D, xk):
         finally:
             if plan is not None:
                 plan.close()
+
+
+def test_bf16_rounding_of_every_class(cg):
+    """fp32 to bf16 in an epilogue: every upper half of an fp32 pattern with lower halves below,
+    at and above the tie, so all exponents, subnormals, overflow to infinity, infinities and NaN."""
+    import torch
+    n, low = 1 << 16, np.array([0x0000, 0x0001, 0x7fff, 0x8000, 0x8001, 0xffff], np.uint32)
+    bits = (np.arange(n, dtype=np.uint32)[:, None] << 16) | low[None, :]
+    x = bits.view(np.float32)
+    rp, cl = dev(np.arange(n + 1, dtype=np.int32)), dev(np.arange(n, dtype=np.int32))
+    Y = cg.spmm(rp, cl, None, dev(x), out_dtype=torch.bfloat16).view(torch.int16).cpu().numpy().view(np.uint16)
+    nan = np.isnan(x)
+    with np.errstate(over="ignore"):
+        want = oracle.round_to(np.where(nan, 0.0, x).astype(np.float64) + 0.0, oracle.BF16).reshape(x.shape)
+    assert np.array_equal(Y[~nan], want[~nan])
+    assert np.all((Y[nan] & 0x7fc0) == 0x7fc0), "a NaN stays a quiet NaN"
+
+
+@pytest.mark.parametrize("k", [9, 11, 15, 67])
+@pytest.mark.parametrize("xk", ["bf16", "f16"])
+def test_linear_tail_keeps_infinities_apart(cg, k, xk):
+    """The streaming kernel's overlapped last slot: an infinity in any feature of one row, or of one
+    output's weights, gives that row or output its infinity and leaves the others finite."""
+    import torch
+    n, m = 2080, 41
+    dt = torch.bfloat16 if xk == "bf16" else torch.float16
+    for d in range(k):
+        X, W = torch.ones((n, k), dtype=dt, device="cuda"), torch.ones((m, k), dtype=dt, device="cuda")
+        X[7, d] = X[n - 1, d] = W[3, d] = W[m - 1, d] = float("inf")
+        want = torch.full((n, m), float(k), device="cuda")
+        want[[7, n - 1], :] = float("inf")
+        want[:, [3, m - 1]] = float("inf")
+        assert torch.equal(cg.linear(X, W, out_dtype=torch.float32), want), d
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("n,H,D,xk", [(1_050_000, 7, 293, "bf16"), (40_000_000, 1, 54, "bf16"), (40_000_000, 3, 9, "f32")])
+def test_ragged_tables_beyond_4gib(cg, n, H, D, xk):
+    """Widths and heads of no whole vector in tables past the 32-bit offsets of the buffer gathers:
+    the sums, max, the aggregation with its weights, dot products and the backward against fp64
+    over the edges, which reach the tables' last rows."""
+    import torch
+    W = H * D
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}[xk]
+    say(f"ragged tables: {n} x {H} x {D} {xk}")
+    assert n * W * (4 if xk == "f32" else 2) > 0xffffff00
+    rng = np.random.default_rng(W)
+    deg = np.zeros(n, np.int64)
+    rows = np.unique(np.concatenate([[0, n - 1, n - 2], rng.choice(n, 200)]))
+    deg[rows] = rng.integers(1, 30, rows.size)
+    deg[n - 2] = 700
+    rowptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    nnz = int(rowptr[-1])
+    cols = np.unique(np.concatenate([[0, n - 1, n - 2], rng.choice(n, 900)]))
+    col = np.concatenate([np.sort(rng.choice(cols, int(deg[r]), replace=False)) for r in rows]).astype(np.int32)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(W)
+    X, G = (torch.randn((n, H, D), dtype=dt, device="cuda", generator=g) for _ in range(2))
+    sd, ss = (torch.randn((n, H), device="cuda", generator=g) for _ in range(2))
+    val = torch.randn(nnz, device="cuda", generator=g)
+    rp, cl = dev(rowptr), dev(col)
+    ri, ci = torch.from_numpy(np.repeat(rows, deg[rows])).cuda(), cl.long()
+    at = torch.from_numpy(rows).cuda()
+    seg = torch.from_numpy(np.repeat(np.arange(rows.size), deg[rows])).cuda()
+
+    def over_rows(t):                                  # sums of per-edge values over the rows with edges
+        return torch.zeros((rows.size,) + tuple(t.shape[1:]), dtype=torch.float64, device="cuda").index_add_(0, seg, t)
+
+    x, p = X[ci].double(), G[ri].double()              # [nnz, H, D]
+    e = torch.nn.functional.leaky_relu((sd[ri] + ss[ci]).double(), 0.2)
+    top = torch.full((rows.size, H), -float("inf"), dtype=torch.float64, device="cuda")
+    top = top.index_reduce_(0, seg, e, "amax")
+    al = torch.exp(e - top[seg])
+    al = al / over_rows(al)[seg]
+    msg = val.double()[:, None, None] * x
+    da, dab = (p * x).sum(-1), (p * x).abs().sum(-1)
+    c, cab = over_rows(al * da), over_rows(al * dab)
+    f = torch.where((sd[ri] + ss[ci]) > 0, 1.0, 0.2).double()
+    ds, dsab = f * al * (da - c[seg]), f * al * (dab + cab[seg])
+    colptr, row_t, _, perm = cg.csr_to_csc(rp, cl, None, n)
+
+    def close(got, want, scale, what, tol=TOL_F32):
+        err = ((got.double() - want).abs() / scale.clamp_min(1e-30)).max().item()
+        assert err <= tol, (n, H, D, xk, what, err)
+
+    for kw in (None, {"mode": "neighbor_group", "group_size": 64}):
+        plan = None if kw is None else cg.Plan(rp, nnz, max_feat=W, max_heads=H, **kw)
+        try:
+            Y = cg.spmm(rp, cl, val, X.view(n, W), plan=plan, out_dtype=torch.float32)
+            close(Y[at], over_rows(msg).view(-1, W), over_rows(msg.abs()).view(-1, W), "sum")
+            del Y
+            M, A = cg.gspmm(rp, cl, val, X.view(n, W), "max", plan=plan, out_dtype=torch.float32, return_arg=True)
+            a = A[at].long()
+            assert torch.all(seg[a] == torch.arange(rows.size, device="cuda")[:, None])
+            picked = (val[a] * X.view(n, W)[ci[a], torch.arange(W, device="cuda")].float())
+            assert torch.equal(M[at], picked)
+            best = torch.full((rows.size, W), -float("inf"), device="cuda")
+            best.index_reduce_(0, seg, (val[:, None] * X.view(n, W)[ci].float()), "amax")
+            assert torch.equal(M[at], best)
+            del M, A
+            Y, alpha = cg.gat_aggregate(rp, cl, sd, ss, X, 0.2, return_alpha=True, plan=plan, out_dtype=torch.float32)
+            want = al[:, :, None] * x
+            close(Y[at].view(-1, W), over_rows(want).view(-1, W), over_rows(want.abs()).view(-1, W), "gat")
+            close(alpha, al, al, "alpha")
+            del Y
+            close(cg.sddmm_dot(rp, cl, G, X, plan=plan), da, dab, "dot")
+            o = cg.gat_backward(rp, cl, colptr, row_t, perm, sd, ss, alpha, X, G, 0.2, plan=plan)
+            close(o["dscore"], ds, dsab, "dscore", 2 * TOL_F32)      # (on the aggregation's own alpha)
+            close(o["ds_dst"][at], over_rows(ds), over_rows(dsab), "ds_dst", 2 * TOL_F32)
+            used = torch.unique(ci)
+            slot = torch.searchsorted(used, ci)
+            wx = torch.zeros((used.numel(), H, D), dtype=torch.float64, device="cuda")
+            dx = wx.clone().index_add_(0, slot, al[:, :, None] * p)
+            dxab = wx.index_add_(0, slot, (al[:, :, None] * p).abs())
+            # (dX in X's format: its half unit in the last place beside the sums' error)
+            close(o["dX"][used].double(), dx, dxab, "dX", 2 * TOL_F32 + (2.0 ** -8 if xk == "bf16" else 0))
+            del o, alpha
+        finally:
+            if plan is not None:
+                plan.close()
+    del X, G
+    torch.cuda.empty_cache()
