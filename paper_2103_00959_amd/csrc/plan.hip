@@ -421,8 +421,8 @@ cogdl_status plan_count(Plan &P, const int32_t *rowptr, const int32_t *col, uint
 
 // Counts, totals, units in row order, the sort by length, the sorted units: five
 // launches beside the sort's three per pass (a build was 20 launches and is now 11 at
-// 12 key bits; column-sliced, 169k rows and 2.5M nonzeros 115 -> 74 us, 2.4M and 122M
-// 396 -> 330 us; plain 84 -> 63 and 194 -> 168 us).
+// 12 key bits; skewed graphs of 170k rows and 2.5M nonzeros, 2.4M and 100M: column-sliced
+// 111 -> 70 and 361 -> 284 us, plain 79 -> 58 and 189 -> 151 us).
 cogdl_status plan_build(Plan &P, const int32_t *rowptr, const int32_t *col, hipStream_t s)
 {
     const int n = P.n_rows;

@@ -30,17 +30,19 @@ constexpr int kBlock = kSpmmBlock;
 
 // Whether the units of a sum run a wavefront each (k_spmm_wave) instead of a group of S
 // lanes.  With a plan: while the units are few enough that the call takes as long as its
-// longest unit, a chain of gathers.  Forward and backward, us, group / wavefront: 12k rows
-// and 100k edges, 64 bf16 62 / 35, 256 bf16 72 / 49; 50k and 500k 95 / 73, 93 / 87; 50k and
-// 2.5M (60k units) 102 / 96, 163 / 178; 100k and 500k 100 / 124.  Rows of under 8 lanes take
-// several edges side by side anyway (16 bf16: 12k rows 35 / 35, 24k 35 / 46).  Without a plan
-// a hub row is one unit, so the chain is far longer (50k rows, 2.5M edges, 64 bf16: 2299 /
-// 524; 169k and 2.5M, 256 bf16: 2400 / 1495), but a graph of even rows loses what their
-// lanes leave empty: there also where the mean row fills half a step's slots (8 slots of
-// 64 / S edges).  Plans cut into groups of under 64 edges have no chains and keep their
-// groups, whether they asked for their mode or choose it (groups of 32, 24k rows and 600k
-// edges, 64 / 256 bf16, 27 / 42 us, a wavefront each 36 / 44), but for graphs so small that
-// the second launch, for the tiny units, shows (15k and 100k edges 18 / 15).
+// longest unit, a chain of gathers.  us, group / wavefront, skewed graphs: 12k rows and 100k
+// edges, 64 bf16 32 / 16, 256 bf16 30 / 19; 24k and 600k, 256 bf16 43 / 27; 50k and 250k
+// 38 / 26, 44 / 31 (even rows of 5 there 19 / 23, 27 / 25); before the kernel fetched ahead,
+// 50k and 2.5M (60k units) 102 / 96, 163 / 178, 100k and 500k 100 / 124, both directions.
+// Rows of under 8 lanes take several edges side by side anyway (16 bf16: 12k rows 35 / 35,
+// 24k 35 / 46).  Without a plan a hub row is one unit, so the chain is far longer (50k rows,
+// 2.5M edges, 64 bf16: 1335 / 177; 170k and 2.5M, 256 bf16: 1096 / 559), but a graph of even
+// rows loses what their lanes leave empty (40k rows of 300, 128 bf16: 164 / 242): there also
+// where the mean row fills half a step's slots (8 slots of 64 / S edges).  Plans cut into
+// groups of under 64 edges have no chains and keep their groups, whether they asked for
+// their mode or choose it (groups of 32, 24k rows and 600k edges, 64 / 256 bf16, 28 / 42 us,
+// a wavefront each 36 / 44), but for graphs so small that the second launch, for the tiny
+// units, shows (15k and 100k edges 18 / 15).
 bool unit_per_wave(const Plan *plan, int S, int64_t units, int64_t nnz)
 {
     if (S >= kWave) return false;
