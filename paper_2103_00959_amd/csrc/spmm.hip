@@ -41,12 +41,13 @@ constexpr int kBlock = kSpmmBlock;
 // where the mean row fills half a step's slots (8 slots of 64 / S edges).  Plans cut into
 // groups of under 64 edges have no chains and keep their groups, whether they asked for
 // their mode or choose it (groups of 32, 24k rows and 600k edges, 64 / 256 bf16, 28 / 42 us,
-// a wavefront each 36 / 44), but for graphs so small that the second launch, for the tiny
-// units, shows (15k and 100k edges 18 / 15).
+// a wavefront each 36 / 44); those that choose it not on graphs so small that the second
+// launch, for the tiny units, shows (15k and 100k edges 18 / 15).
 bool unit_per_wave(const Plan *plan, int S, int64_t units, int64_t nnz)
 {
     if (S >= kWave) return false;
-    if (plan && plan->mode_req != COGDL_BALANCE_ROW_SPLIT && plan->group_size < kWave && nnz > (1 << 18))
+    if (plan && plan->group_size < kWave &&
+        (plan->mode_req == COGDL_BALANCE_NEIGHBOR_GROUP || (plan->mode_req == COGDL_BALANCE_AUTO && nnz > 1 << 18)))
         return false;
     if (units <= (S < 8 ? 8192 : plan ? 55000 : 16384)) return true;
     return !plan && nnz >= units * (256 / S);

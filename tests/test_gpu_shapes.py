@@ -342,8 +342,8 @@ def test_linear_grids(cg, n, k, m):
 @pytest.mark.parametrize("mode", ["auto", "neighbor_group", "row_split"])
 @pytest.mark.parametrize("F,xk", [(41, "bf16"), (64, "bf16"), (33, "f32")])
 def test_spmm_small_groups(cg, n, mode, F, xk):
-    """Plans cut into groups of 32 edges around the size (2^18 edges) from where their units stop
-    running a wavefront each, with the mode asked for and chosen."""
+    """Plans cut into groups of 32 edges around the size (2^18 edges) from where those that chose
+    their mode stop running a wavefront a unit; those that asked for it never do."""
     import torch
     g = _graph(F, n=n, m=3000)
     assert (g.nnz > 1 << 18) == (n == 42000)
